@@ -179,6 +179,17 @@ __device__ __forceinline__ float wave_sum(float x)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
+// max(|a|, |b|, |c|) in one instruction.  Written out because the
+// compiler's own form would first quiet inputs it cannot prove free of
+// signalling NaNs, or lose the third operand across branches.  A NaN operand
+// is passed over, as fmaxf does.
+__device__ __forceinline__ float max3_abs(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // ---------------------------------------------------------------------------
 // decode step
 
@@ -348,6 +359,7 @@ __device__ __forceinline__ float row_constants(const HeadInfo &hi, int dk, float
 // 4 cg .. 4 cg + 3 of pivot rows p = slice + NSL m, as 4 binary16 values.
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 
 // PMAX: the most pivot rows a head of the launch may hold.
 template <int DV, int PMAX = kMaxPivots>
@@ -386,9 +398,9 @@ __device__ __forceinline__ uint32_t pack_halves(float a, float b)
 
 // The pivot rows' share of the column partials, pre-divided by c_j (the
 // column phase multiplies the partials by c_j).
-template <int DV, int PMAX>
+template <int DV, int PMAX, class SH>
 __device__ __forceinline__ void pivot_acc(const TileCtx &t, int slice, int cg, const PivotRegs<DV, PMAX> &pr,
-                                          const DecodeShared<DV> &sh, float (&acK)[4], float (&acQ)[4])
+                                          const SH &sh, float (&acK)[4], float (&acQ)[4])
 {
     if (t.hi.n16 == 0) return;
     const float4 c4 = *reinterpret_cast<const float4 *>(&sh.cpiv[4 * cg]);
@@ -412,9 +424,9 @@ __device__ __forceinline__ void pivot_acc(const TileCtx &t, int slice, int cg, c
 
 // New pivot values X_pj = d_i S_pj + beta k_i delta_j in binary16, stored in
 // place (delta_j = bc_j c_j).
-template <int DV, int PMAX>
+template <int DV, int PMAX, class SH>
 __device__ __forceinline__ void pivot_update(const TileCtx &t, int slice, int cg, const PivotRegs<DV, PMAX> &pr,
-                                             const DecodeShared<DV> &sh, const float (&bc)[4])
+                                             const SH &sh, const float (&bc)[4])
 {
     if (t.hi.n16 == 0) return;
     const float4 c4 = *reinterpret_cast<const float4 *>(&sh.cpiv[4 * cg]);
@@ -668,9 +680,9 @@ __device__ __forceinline__ float row_constants_mfma_piv(const HeadInfo &hi, floa
 // Column sums of the per-thread partials, residual, readout, column factor
 // of the code-space update.  cj, vj: column tid's scale and value (threads
 // < DV, loaded at the start of the tile).  Ends with a barrier.
-template <int DV>
-__device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta,
-                                            DecodeShared<DV> &sh, float kappa, float cj, float vj);
+template <int DV, class SH>
+__device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta, SH &sh,
+                                            float kappa, float cj, float vj);
 
 template <int DV>
 __device__ __forceinline__ void column_phase(const DecodeArgs &a, int tile, float alpha, float beta,
@@ -685,9 +697,9 @@ __device__ __forceinline__ void column_phase(const DecodeArgs &a, int tile, floa
 }
 
 // The column phase once every thread has written its partials to sh.red.
-template <int DV>
-__device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta,
-                                            DecodeShared<DV> &sh, float kappa, float cj, float vj)
+template <int DV, class SH>
+__device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta, SH &sh,
+                                            float kappa, float cj, float vj)
 {
     constexpr int NSL = 256 / (DV / 4);
     const int tid = threadIdx.x;
@@ -930,8 +942,8 @@ __device__ __forceinline__ f32x4 mfma_view(const _Float16 (&A)[4][4], const uint
 // and their slot views (one accumulator live), written to LDS unscaled.
 // The slot-0 views of the group holding the width boundary (vb) come in
 // formed; the other views are formed again for each column rather than kept.
-template <int E>
-__device__ __forceinline__ void rowmix_column(const DecodeShared<128> &sh, const uint32_t (&w)[16],
+template <int E, class W>
+__device__ __forceinline__ void rowmix_column(const DecodeShared<128> &sh, const W &w,
                                               const uint32_t (&vb)[4], int slice, int cg, int g8, int ng, int ek,
                                               int eq, float *redK, float *redQ)
 {
@@ -966,7 +978,8 @@ __device__ __forceinline__ void rowmix_column(const DecodeShared<128> &sh, const
 // word groups (four accumulators live): each group's slot views are formed
 // once rather than once per column.  For bodies whose register peak lies
 // after the column phase (the refitting body).
-__device__ __forceinline__ void rowmix_columns4(const DecodeShared<128> &sh, const uint32_t (&w)[16], int slice,
+template <class W>
+__device__ __forceinline__ void rowmix_columns4(const DecodeShared<128> &sh, const W &w, int slice,
                                                 int cg, int g8, int ng, int ek, int eq, float *redK, float *redQ)
 {
     f32x4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = d0, d2 = d0, d3 = d0;
@@ -1018,10 +1031,10 @@ __device__ __forceinline__ void rowmix_columns4(const DecodeShared<128> &sh, con
 // thread's 16 code words (0 past the head's last group); pr: its pivot row.
 // ALLCOLS: the four columns in one pass (rowmix_columns4), else one at a
 // time (fewer registers).
-template <bool DIAG, bool SCALED, bool ALLCOLS = false>
+template <bool DIAG, bool SCALED, bool ALLCOLS = false, class W, class F>
 __device__ __forceinline__ void rowmix_sums(const DecodeArgs &a, const TileCtx &t, DecodeShared<128> &sh,
-                                            const uint32_t (&w)[16], const PivotRegs<128, kCompactPivots> &pr,
-                                            const RowColOps &op, int g8, int ng)
+                                            const W &w, const PivotRegs<128, kCompactPivots> &pr,
+                                            const RowColOps &op, int g8, int ng, F &&constants_done)
 {
     const int tid = threadIdx.x;
     const int cg = tid & 31, slice = tid >> 5;
@@ -1029,6 +1042,7 @@ __device__ __forceinline__ void rowmix_sums(const DecodeArgs &a, const TileCtx &
     // rows), so neither is held in registers through the row sums
     if (tid < 128) sh.bcol[tid] = op.v;
     const float kappa = uniform_f(row_constants<DIAG, 128, SCALED>(t.hi, 128, t.alpha, t.beta, op, sh, a.pool.lv));
+    constants_done();
     int ek, eq;
     row_operands_rowmix(t.hi, sh, ek, eq);
 

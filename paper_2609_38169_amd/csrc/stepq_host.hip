@@ -348,6 +348,7 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
     };
     hipError_t e = hipSuccess;
     const stepq::LaunchPlan &plan = p->plan;
+    a.pairs = plan.pairs;
     // the combined launches the refit has bodies for: several uniform layouts
     // and whole FP16 heads, or one uniform layout and its padded pivot heads
     const bool refit_multi = (flags & STEPQ_STEP_REFIT) && stepq::refit_combined(plan.mixed_code);
@@ -369,6 +370,7 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
         for (size_t c = 0; c < plan.cls_code.size() && e == hipSuccess; ++c) {
             a.head_list = p->d_head_order + plan.cls_off[c];
             a.n_heads = plan.cls_cnt[c];
+            a.pairs = plan.cls_pairs[c];
             a.div_heads = fast_div(static_cast<uint32_t>(plan.cls_cnt[c]));
             e = launch(plan.cls_code[c]);
         }

@@ -85,6 +85,26 @@ constexpr int kMultiPivot = 41;
 // heads keep layout 0 in their HeadInfo.
 constexpr int kRowMix = 42;
 
+// The slot bodies (any row-width mix) hold a thread's rows in pairs of row
+// slots: the 8-bit words of a slice two to a pair, a 4-bit word in one pair,
+// a 2-bit word in two, from an even pair on.  Pairs that a head of g8 / g4 /
+// g2 row groups takes with nsl slices (8 at d_v = 128, 16 at d_v = 64).
+constexpr int slot_pairs(int g8, int g4, int g2, int nsl)
+{
+    const int ints = ((g8 + nsl - 1) / nsl + 1) / 2 + (g4 + nsl - 1) / nsl;
+    return g2 == 0 ? ints : (ints + 1) / 2 * 2 + 2 * ((g2 + nsl - 1) / nsl);
+}
+// The most pairs any head takes: row-mix heads (8- and 4-bit rows, d_v =
+// 128), any head at d_v = 128, any head at d_v = 64; and the sizes compiled.
+constexpr int kSlotPairs84 = 9;
+constexpr int kSlotPairsAny = 12;
+constexpr int kSlotPairs64 = 8;
+constexpr int slot_pairs_compiled(int pairs, int dv)
+{
+    if (dv == 64) return pairs <= 4 ? 4 : (pairs <= 6 ? 6 : kSlotPairs64);
+    return pairs <= 6 ? 6 : (pairs <= 8 ? 8 : (pairs <= 10 ? 10 : kSlotPairsAny));
+}
+
 // One value head of a decode launch over part of a pool's heads: its index
 // and the byte offset of its tile within a slot record.
 struct LaunchHead {

@@ -35,6 +35,8 @@ bool rowmix_head(const HeadInfo &hi, int dk)
 
 int32_t packed_counts(const HeadInfo &hi) { return static_cast<int32_t>(hi.n16 | (hi.n8 << 8) | (hi.n4 << 16)); }
 
+int head_pairs(const HeadInfo &hi, int dv) { return slot_pairs(hi.g8, hi.g4, hi.g2, dv == 128 ? 8 : 16); }
+
 bool fail_check(std::string *err, const std::string &msg)
 {
     if (err) *err = msg;
@@ -159,6 +161,7 @@ void plan_launches(const std::vector<HeadInfo> &heads, int dk, int dv, LaunchPla
     plan->layout = static_cast<int>(heads[0].layout);
     for (const HeadInfo &hi : heads)
         if (static_cast<int>(hi.layout) != plan->layout) plan->layout = 0;
+    for (const HeadInfo &hi : heads) plan->pairs = std::max(plan->pairs, head_pairs(hi, dv));
     // padded pivot heads differ in their row counts, which travel in the head list
     if (plan->layout > kPivotUniformBase) plan->layout = 0;
     if (plan->layout != 0 || dv != 128) return;
@@ -192,12 +195,15 @@ void plan_launches(const std::vector<HeadInfo> &heads, int dk, int dv, LaunchPla
         plan->cls_code.push_back(code);
         plan->cls_off.push_back(static_cast<int>(plan->order.size()));
         plan->cls_cnt.push_back(-c.first);
+        int pairs = 0;
         for (size_t h = 0; h < heads.size(); ++h) {
             const HeadInfo &hi = heads[h];
             if (static_cast<int>(hi.layout) != c.second) continue;
             plan->order.push_back({static_cast<int32_t>(h), hi.tile_off, static_cast<int32_t>(hi.layout),
                                    packed_counts(hi)});
+            pairs = std::max(pairs, head_pairs(hi, dv));
         }
+        plan->cls_pairs.push_back(pairs);
     }
     // one uniform class of layout 1 or 2 whose other classes are its padded
     // pivot heads, compact generic or whole FP16 heads: a decode step is one
@@ -293,6 +299,11 @@ bool check_plan(const LaunchPlan &plan, const std::vector<HeadInfo> &heads, int 
 {
     const int Hv = static_cast<int>(heads.size());
     if (Hv < 1) return fail_check(err, "no heads");
+    // the slot bodies hold every head of the launches they may get
+    const int max_pairs = dv == 128 ? kSlotPairsAny : kSlotPairs64;
+    int pool_pairs = 0;
+    for (const HeadInfo &hi : heads) pool_pairs = std::max(pool_pairs, head_pairs(hi, dv));
+    if (plan.pairs != pool_pairs || pool_pairs > max_pairs) return fail_check(err, "row pairs of the pool");
     // the head records tile the slot record
     size_t off = 0;
     for (int h = 0; h < Hv; ++h) {
@@ -346,7 +357,7 @@ bool check_plan(const LaunchPlan &plan, const std::vector<HeadInfo> &heads, int 
         if (lh.counts != packed_counts(hi)) return fail_check(err, at + "row counts differ");
     }
     const size_t nc = plan.cls_code.size();
-    if (nc == 0 || plan.cls_off.size() != nc || plan.cls_cnt.size() != nc)
+    if (nc == 0 || plan.cls_off.size() != nc || plan.cls_cnt.size() != nc || plan.cls_pairs.size() != nc)
         return fail_check(err, "class tables missing or of different lengths");
     int next = 0;
     for (size_t c = 0; c < nc; ++c) {
@@ -359,6 +370,9 @@ bool check_plan(const LaunchPlan &plan, const std::vector<HeadInfo> &heads, int 
             const HeadInfo &hi = heads[plan.order[e].h];
             if (!decode_body_runs(plan.cls_code[c], hi, dk))
                 return fail_check(err, at + "its decode body does not run head " + std::to_string(plan.order[e].h));
+            if (head_pairs(hi, dv) > plan.cls_pairs[c] ||
+                (plan.cls_code[c] == kRowMix && head_pairs(hi, dv) > kSlotPairs84))
+                return fail_check(err, at + "head " + std::to_string(plan.order[e].h) + " has more row pairs");
             if (!refit_body_runs(plan.cls_code[c], hi, dk))
                 return fail_check(err, at + "its refitting body does not run head " + std::to_string(plan.order[e].h));
         }

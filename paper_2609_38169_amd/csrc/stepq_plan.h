@@ -30,6 +30,9 @@ struct LaunchPlan {
     std::vector<LaunchHead> order;
     std::vector<int> cls_code, cls_off, cls_cnt;
     int mixed_code = 0;
+    // the most slot_pairs of a head: of the whole pool, and per class
+    int pairs = 0;
+    std::vector<int> cls_pairs;
 };
 
 // Validate a descriptor and derive the per-head layout records and the

@@ -30,7 +30,7 @@
 // uniform layouts have a lean body of their own for it (stepq_rowmax.hip).
 #pragma once
 
-#include "stepq_device.h"
+#include "stepq_slots.h"
 
 #include <type_traits>
 
@@ -87,8 +87,8 @@ __device__ __forceinline__ float row_partial(const float *y, const float (&cc)[4
     }
 }
 
-// Row slot x (physical row p, width bw, old scale r_p): r' from the lane
-// partials, written to the tile; h and W to LDS.  The partials are sums (or
+// A row of width bw and old scale r_p: r' from its PR lane partials, and h
+// and W.  The partials are sums (or
 // maxima) of c_j |y_ij| with y = X / (r c nu), nu the width's level step:
 // the mean |X_ij| is r nu sum / d_v, W = (w r' nu)^2, and the row-absmax
 // factor r' = r max / q_b puts the row's largest entry on the top level in
@@ -96,37 +96,36 @@ __device__ __forceinline__ float row_partial(const float *y, const float (&cc)[4
 // factors are formed with the hardware reciprocal and square root (about one
 // ulp each): every later step uses the stored fp32 values, so the codes stay
 // consistent with them.
-template <int DV, Refit MODE>
-__device__ __forceinline__ void refit_row(RefitShared<DV> &sh, int x, int p, int bw, float r_p, float *rr_out,
-                                          const LevelTable &lv)
+template <Refit MODE, int PR>
+__device__ __forceinline__ float refit_row(const float4 *part, int bw, float r_p, float w, const LevelTable &lv,
+                                           float &h, float &W)
 {
     const float iq = bw == 8 ? (1.0f / 127.0f) : (bw == 4 ? (1.0f / 7.0f) : 1.0f);     // 1 / q_b
     const float nu = lv.nu[bw == 8 ? 0 : (bw == 4 ? 1 : 2)];
     if constexpr (MODE == Refit::RowAbsmax) {
         float mx = 0.f;
 #pragma unroll
-        for (int l = 0; l < DV / 8; l += 4) {
-            const float4 v4 = *reinterpret_cast<const float4 *>(&sh.u.rowp[x][l]);
+        for (int l = 0; l < PR / 4; ++l) {
+            const float4 v4 = part[l];
             mx = fmaxf(mx, fmaxf(fmaxf(v4.x, v4.y), fmaxf(v4.z, v4.w)));
         }
         const float rn = fmaxf((r_p * iq) * mx, kScaleFloor);
-        sh.hrow[x] = r_p * __builtin_amdgcn_rcpf(rn);
-        rr_out[p] = rn;
-        return;
+        h = r_p * __builtin_amdgcn_rcpf(rn);
+        W = 0.f;
+        return rn;
     }
     float sum = 0.f;
 #pragma unroll
-    for (int l = 0; l < DV / 8; l += 4) {
-        const float4 v4 = *reinterpret_cast<const float4 *>(&sh.u.rowp[x][l]);
+    for (int l = 0; l < PR / 4; ++l) {
+        const float4 v4 = part[l];
         sum += (v4.x + v4.y) + (v4.z + v4.w);
     }
-    const float m = (r_p * nu) * (sum * (1.0f / static_cast<float>(DV)));
-    const float w = sh.wphys[p];
+    const float m = (r_p * nu) * (sum * (1.0f / static_cast<float>(8 * PR)));
     const float rn = fmaxf(__builtin_amdgcn_sqrtf(m * __builtin_amdgcn_rcpf(w)), kScaleFloor);
-    sh.hrow[x] = r_p * __builtin_amdgcn_rcpf(rn);
+    h = r_p * __builtin_amdgcn_rcpf(rn);
     const float t = (w * rn) * nu;
-    sh.wrow[x] = t * t;
-    rr_out[p] = rn;
+    W = t * t;
+    return rn;
 }
 
 // Per-thread column maxima of |yh| kept per width, divided by q_b once.
@@ -139,8 +138,8 @@ __device__ __forceinline__ float4 width_max(const float (&m8)[4], const float (&
 }
 
 // Column j: absmax start c0_j from the slice maxima; e_j = c_j / c0_j.
-template <int DV>
-__device__ __forceinline__ void refit_colmax(RefitShared<DV> &sh, int j)
+template <int DV, class SH>
+__device__ __forceinline__ void refit_colmax(SH &sh, int j)
 {
     constexpr int NSL = 256 / (DV / 4);
     const float *mx = reinterpret_cast<const float *>(&sh.u.cmax[0][0]);
@@ -153,8 +152,8 @@ __device__ __forceinline__ void refit_colmax(RefitShared<DV> &sh, int j)
 }
 
 // Column j: the least-squares column factor from the slice sums in d.red.
-template <int DV>
-__device__ __forceinline__ void refit_colfit(RefitShared<DV> &sh, int j, float *cc_out)
+template <int DV, class SH>
+__device__ __forceinline__ void refit_colfit(SH &sh, int j, float *cc_out)
 {
     constexpr int NSL = 256 / (DV / 4);
     const float *rn = reinterpret_cast<const float *>(&sh.d.red[0][0][0]);
@@ -259,24 +258,27 @@ __device__ __forceinline__ void word_scale_max(float *Y, const float *hrow, int 
     }
 }
 
+// One row's share of the least-squares sums (4 columns).
+__device__ __forceinline__ void row_fit(const float *Y, float W, const float (&ec)[4], float (&num)[4], float (&den)[4])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float yh = Y[e];
+        // round to nearest even by the fp32 grid at 1.5 2^23 (|z| <= q_b):
+        // one rounding of the exact product, in two full-rate operations
+        const float z = fmaf(yh, ec[e], kRoundMagic) - kRoundMagic;
+        const float u = W * z;
+        num[e] = fmaf(u, yh, num[e]);
+        den[e] = fmaf(u, z, den[e]);
+    }
+}
+
 template <int B>
 __device__ __forceinline__ void word_fit(const float *Y, const float *wrow, int x0, const float (&ec)[4],
                                          float (&num)[4], float (&den)[4])
 {
 #pragma unroll
-    for (int s = 0; s < 8 / B; ++s) {
-        const float W = wrow[x0 + s];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float yh = Y[4 * s + e];
-            // round to nearest even by the fp32 grid at 1.5 2^23 (|z| <= q_b):
-            // one rounding of the exact product, in two full-rate operations
-            const float z = fmaf(yh, ec[e], kRoundMagic) - kRoundMagic;
-            const float u = W * z;
-            num[e] = fmaf(u, yh, num[e]);
-            den[e] = fmaf(u, z, den[e]);
-        }
-    }
+    for (int s = 0; s < 8 / B; ++s) row_fit(Y + 4 * s, wrow[x0 + s], ec, num, den);
 }
 
 // New word: per field round(yh g_j) clamped to +-q_b, packed with a bias of
@@ -391,13 +393,16 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
             int bw;
             const int p = slot_row(t.hi, tid, bw);
             if (p >= 0) {
-                refit_row<128, MODE>(sh, tid, p, bw, sh.d.sr[p], rr_out, a.pool.lv);
+                rr_out[p] = refit_row<MODE, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]), bw, sh.d.sr[p],
+                                                sh.wphys[p], a.pool.lv, sh.hrow[tid], sh.wrow[tid]);
             } else {
                 sh.hrow[tid] = 0.f;
                 sh.wrow[tid] = 0.f;
             }
         } else {
-            refit_row<128, MODE>(sh, tid, tid, tid < X4 ? 8 : (tid < X2 ? 4 : 2), op.r, rr_out, a.pool.lv);
+            rr_out[tid] = refit_row<MODE, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]),
+                                              tid < X4 ? 8 : (tid < X2 ? 4 : 2), op.r, sh.wphys[tid], a.pool.lv,
+                                              sh.hrow[tid], sh.wrow[tid]);
         }
     }
     __syncthreads();
@@ -448,359 +453,291 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
         cw.store_m(tid, M8 + M4 + m, word_requant<2>(&Y[Y2 + 16 * m], g));
 }
 
-// ---- any row-width mix and d_v: the words stay packed in registers and
-// each pass unpacks them again.
+// ---- heads of any mix (the slot bodies of stepq_slots.h): the thread's rows
+// in NP pairs of slots, all values in registers through the passes as in the
+// uniform body.  Slots without a row have al = av = 0, so y = 0 there, and
+// h = W = 0: they add nothing to the sums and maxima.
+//
+// Bound by VALU issue (about 4.6 cycles per wave64 instruction and SIMD, in
+// every instruction class of these bodies), so what counts is the number of
+// instructions.  Keeping the values and taking the width tests as scalar
+// branches, against bodies that unpacked the words again in each pass
+// (generic) or tested each lane's width in each word-step (row-mix): a
+// 512-request x 16-head row-unit map with channel-wise gates 120.7 -> 101.4 us
+// (1,942 -> 1,645 instructions per wave), 201 requests x 6 heads of random
+// 2/4/8-bit rows at d_k = 96, d_v = 64 16.0 -> 14.3 us.
 
-template <int B, bool DIAG, int DV>
-__device__ __forceinline__ void gen_word_y(uint32_t w, const DecodeShared<DV> &d, int x0, float alpha,
-                                           const float (&bc)[4], float (&Y)[16])
+// ROWMIX: the first half is the frozen row-mix body's (rowmix_sums, with its
+// own row tables in d); the slot constants are then copies of those.
+template <int DV, int NP, bool ROWMIX>
+struct SlotRefitShared {
+    using D = SlotShared<DV, NP>;
+    static constexpr int PR = DV / 8;              // partials per row: one per column-lane pair
+    typename std::conditional<ROWMIX, DecodeShared<128>, D>::type d;
+    union {
+        // partials of sum_j c_j |y_ij| by slice and slot; the slices' tables
+        // are PR floats apart from a multiple of the banks
+        float rowp[D::NSL][(D::NR + 1) * PR];
+        float4 cmax[D::NSL][D::CG];
+    } u;
+    alignas(16) float av[ROWMIX ? D::NSL : 1][D::NR], al[ROWMIX ? D::NSL : 1][D::NR];
+    alignas(16) float hrow[D::NSL][D::NR];         // r_i / r'_i (0 for slots without a row)
+    alignas(16) float wrow[D::NSL][D::NR];         // W_i
+    float ccol[DV], ecol[DV], gcol[DV];            // c_j, c_j / c0_j, c_j / c'_j
+};
+
+// The row partial of slot r, combined with the neighbouring lane's (the next
+// 4 columns of the row); both lanes of a pair write the same value.
+template <Refit MODE>
+__device__ __forceinline__ void put_slot_partial(float *rowp, int r, int pr, float acc)
 {
-    float U[16];
-    unpack_word<B>(w, U);
-    const float al_w = alpha * (B == 8 ? 1.0f : (B == 4 ? (1.0f / 16.0f) : (1.0f / 64.0f)));
-#pragma unroll
-    for (int s = 0; s < 8 / B; ++s) {
-        const float a_s = d.av[x0 + s];
-        const float al = DIAG ? d.al[x0 + s] : al_w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) Y[4 * s + e] = fmaf(al, U[4 * s + e], a_s * bc[e]);
-    }
+    if constexpr (MODE == Refit::DualAxis) acc += dpp_term<0xB1, 0xF>(acc);    // quad_perm [1,0,3,2]
+    else acc = __uint_as_float(max(__float_as_uint(acc), dpp_bits<0xB1, 0xF>(__float_as_uint(acc))));
+    rowp[r * pr] = acc;
 }
 
-// Calls f(width constant, group geometry, word index) for every word of the
-// thread that holds codes.
-template <int DV, class F>
-__device__ __forceinline__ void each_word(const TileCtx &t, int slice, F &&f)
+// Slots of B-bit rows from Y (4 columns each), packed without the bias flip.
+template <int B, int NS>
+__device__ __forceinline__ uint32_t requant_rows(const float *Y, const float (&g)[4])
 {
-    constexpr int NSL = 256 / (DV / 4);
-    constexpr int MMAX = kMaxDk * (DV / 4) / 256;
-    const int ngroups = static_cast<int>(t.hi.groups);
+    constexpr float bias = static_cast<float>(1 << (B - 1));
+    constexpr float top = static_cast<float>((1 << B) - 1);
+    uint32_t out = 0;
 #pragma unroll
-    for (int m = 0; m < MMAX; ++m) {
-        const int g = slice + NSL * m;
-        if (g < ngroups) {
-            const GroupRows gr = group_rows(t.hi, g);
-            if (gr.bits == 8) f(std::integral_constant<int, 8>(), gr, m);
-            else if (gr.bits == 4) f(std::integral_constant<int, 4>(), gr, m);
-            else f(std::integral_constant<int, 2>(), gr, m);
+    for (int s = 0; s < NS; ++s) {
+        uint32_t P = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            P = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(fmaf(Y[4 * s + e], g[e], bias), 1.0f, top), e, P);
+        out |= P << (s * B);
+    }
+    return out;
+}
+
+// The unpacked fields of the thread's rows as fp32, in the registers that
+// hold the values afterwards.
+template <int NP, bool HAS2>
+__device__ __forceinline__ void slot_fields(const SlotGeom &g, const uint32_t (&wa)[NP], const uint32_t (&wb)[NP],
+                                            float (&Y)[NP][8])
+{
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        uint32_t lo, hi;
+        slot_views<NP, HAS2>(g, wa, wb, p, lo, hi);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            Y[p][e] = sbyte(lo, e);
+            Y[p][4 + e] = sbyte(hi, e);
         }
     }
 }
 
-template <bool BF16, bool DIAG, int DV, Refit MODE>
-__device__ __forceinline__ void refit_generic(const DecodeArgs &a, const TileCtx &t, RefitShared<DV> &sh)
+template <bool BF16, bool DIAG, int DV, int NP, bool HAS2, int PMAX, Refit MODE, bool ROWMIX>
+__device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &t, SlotRefitShared<DV, NP, ROWMIX> &sh)
 {
-    constexpr int CG = DV / 4;
-    constexpr int NSL = 256 / CG;
-    constexpr int MMAX = kMaxDk * CG / 256;
+    using SH = SlotRefitShared<DV, NP, ROWMIX>;
+    using D = typename SH::D;
     const int tid = threadIdx.x;
-    const int cg = tid % CG, slice = tid / CG;
-    const int ngroups = static_cast<int>(t.hi.groups);
+    const int cg = tid % D::CG, slice = tid / D::CG;
     const int dk = a.pool.dk;
     float *rr_out = const_cast<float *>(t.rr);
     float *cc_out = const_cast<float *>(t.cc);
-    const CodeWords cw(t.codes, t.hi.piv_off);
-    uint32_t w[MMAX];
+    const SlotGeom g(t.hi, D::NSL == 8 ? 3 : 4);
+    const SlotWords<DV> cw(t.codes, g, slice);
+    uint32_t wa[NP], wb[NP];
+    u32x16 w16;
+    const int ng = g.g8 + g.g4;
+    if constexpr (ROWMIX) {
+        // the codes region only (128 ng bytes): words past the head's last group read 0
+        const CodeWords all(t.codes, t.hi.piv_off);
 #pragma unroll
-    for (int m = 0; m < MMAX; ++m) {
-        const int g = slice + NSL * m;
-        w[m] = g < ngroups ? cw.load(tid + 256 * m) : 0u;
+        for (int m = 0; m < 16; ++m) w16[m] = 8 * m < ng ? all.load(tid + 256 * m) : 0u;
+    } else {
+        slot_load<DV, NP, HAS2>(cw, g, wa, wb);
     }
-    PivotRegs<DV> pr;
+    PivotRegs<DV, PMAX> pr;
     pivot_load(t, slice, cg, pr);
     const RowColOps op = load_ops<BF16, DIAG, DV>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    const SlotRow row = slot_of_row<D::NSL>(t.hi, g, tid, dk);
+    float w_row = 1.0f;
+    if (MODE == Refit::DualAxis && row.slice >= 0) w_row = a.pool.roww[t.h * dk + tid];
     if (tid < DV) sh.ccol[tid] = op.c;
-    if (tid < dk) sh.wphys[tid] = a.pool.roww[t.h * dk + tid];
-    const float kappa = row_constants<DIAG, DV>(t.hi, dk, t.alpha, t.beta, op, sh.d, a.pool.lv);
+    if (tid < D::NSL * D::NR) {
+        (&sh.hrow[0][0])[tid] = 0.f;
+        (&sh.wrow[0][0])[tid] = 0.f;
+        if constexpr (ROWMIX) {
+            (&sh.av[0][0])[tid] = 0.f;
+            (&sh.al[0][0])[tid] = 0.f;
+        }
+    }
+    // The row sums keep the order of the rows (8-, 4-, then 2-bit words of the
+    // slice, then the slices): a fixed code of the fit that lies near a
+    // rounding boundary depends on their last bits.
+    float Y[NP][8];
+    if constexpr (ROWMIX) {
+        rowmix_sums<DIAG, false, true>(a, t, sh.d, w16, pr, op, g.g8, ng, [&] {
+            if (row.slice >= 0) {
+                // row-table slot of physical row tid: the integer rows in order
+                const int x = tid - static_cast<int>(t.hi.n16);
+                sh.av[row.slice][row.r] = sh.d.av[x];
+                sh.al[row.slice][row.r] = DIAG ? sh.d.al[x] : (row.bw == 8 ? t.alpha : t.alpha * (1.0f / 16.0f));
+            }
+        });
+        // the words by class: 8-bit word-step m is m, a slice's 4-bit words
+        // follow its 8-bit ones (one earlier in slices past the class's end)
+        const bool early = g.g8 % 8 != 0 && slice >= g.g8 % 8;
+        const int m4 = (g.g8 + 7) >> 3;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            wa[p] = wb[p] = 0u;
+            if (p < g.p4) {
+                wa[p] = 2 * p < 16 ? w16[2 * p < 16 ? 2 * p : 0] : 0u;
+                wb[p] = 2 * p + 1 < 16 ? w16[2 * p + 1 < 16 ? 2 * p + 1 : 0] : 0u;
+            } else if (p < g.pt) {
+                const int i = m4 + p - g.p4;
+                const uint32_t late = i < 16 ? w16[i & 15] : 0u, soon = w16[(i - 1) & 15];
+                wa[p] = early ? soon : late;
+            }
+        }
+        slot_fields<NP, HAS2>(g, wa, wb, Y);
+    } else {
+        const float kappa = slot_constants<DIAG>(t.hi, dk, t.alpha, t.beta, op, sh.d, a.pool.lv, row);
+        slot_fields<NP, HAS2>(g, wa, wb, Y);
+        float acK[4] = {0.f, 0.f, 0.f, 0.f}, acQ[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const float4 c = *reinterpret_cast<const float4 *>(&sh.d.kq[slice][2 * p]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acK[e] = fmaf(c.z, Y[p][4 + e], fmaf(c.x, Y[p][e], acK[e]));
+                acQ[e] = fmaf(c.w, Y[p][4 + e], fmaf(c.y, Y[p][e], acQ[e]));
+            }
+        }
+        pivot_acc(t, slice, cg, pr, sh.d, acK, acQ);
+        sh.d.red[0][slice][cg] = make_float4(acK[0], acK[1], acK[2], acK[3]);
+        sh.d.red[1][slice][cg] = make_float4(acQ[0], acQ[1], acQ[2], acQ[3]);
+        column_sums<DV>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh.d, kappa, sh.d.cpiv[tid & (DV - 1)],
+                        sh.d.bcol[tid & (DV - 1)]);
+    }
 
-    float acK[4] = {0.f, 0.f, 0.f, 0.f}, acQ[4] = {0.f, 0.f, 0.f, 0.f};
-    each_word<DV>(t, slice, [&](auto bw, const GroupRows &gr, int m) {
-        float U[16];
-        unpack_acc<decltype(bw)::value>(w[m], sh.d.kq, gr.x0, U, acK, acQ);
-    });
-    pivot_acc(t, slice, cg, pr, sh.d, acK, acQ);
-    column_phase<DV>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh.d, kappa, acK, acQ, op.c, op.v);
-
+    // pass 1: y on the old scales and the row partials
     float bc[4], cc[4];
     ld4(&sh.d.bcol[4 * cg], bc);
     ld4(&sh.ccol[4 * cg], cc);
     pivot_update(t, slice, cg, pr, sh.d, bc);      // pivot rows take no part in the fits
-
-    // pass 1: row partials straight to LDS (one entry per lane pair and slot)
-    each_word<DV>(t, slice, [&](auto bw, const GroupRows &gr, int m) {
-        constexpr int B = decltype(bw)::value;
-        float Y[16];
-        gen_word_y<B, DIAG, DV>(w[m], sh.d, gr.x0, t.alpha, bc, Y);
+    const float *avs, *als;
+    if constexpr (ROWMIX) {
+        avs = sh.av[slice];
+        als = sh.al[slice];
+    } else {
+        avs = sh.d.av[slice];
+        als = sh.d.al[slice];
+    }
+    float *rowp = &sh.u.rowp[slice][cg >> 1];
 #pragma unroll
-        for (int s = 0; s < 8 / B; ++s) put_row_partial<DV, MODE>(sh, gr.x0 + s, cg, row_partial<MODE>(&Y[4 * s], cc));
-    });
-    __syncthreads();
-    if (tid < kSlotTable) {
-        int bw;
-        const int p = slot_row(t.hi, tid, bw);
-        if (p >= 0) {
-            refit_row<DV, MODE>(sh, tid, p, bw, sh.d.sr[p], rr_out, a.pool.lv);
-        } else {
-            sh.hrow[tid] = 0.f;
-            sh.wrow[tid] = 0.f;
+    for (int p = 0; p < NP; ++p) {
+        const float2 as = *reinterpret_cast<const float2 *>(avs + 2 * p);
+        const float2 ag = *reinterpret_cast<const float2 *>(als + 2 * p);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            Y[p][e] = fmaf(ag.x, Y[p][e], as.x * bc[e]);
+            Y[p][4 + e] = fmaf(ag.y, Y[p][4 + e], as.y * bc[e]);
         }
+        put_slot_partial<MODE>(rowp, 2 * p, SH::PR, row_partial<MODE>(&Y[p][0], cc));
+        put_slot_partial<MODE>(rowp, 2 * p + 1, SH::PR, row_partial<MODE>(&Y[p][4], cc));
+    }
+    __syncthreads();
+    if (row.slice >= 0) {
+        const float4 *part = reinterpret_cast<const float4 *>(&sh.u.rowp[row.slice][row.r * SH::PR]);
+        float h, W;
+        rr_out[tid] = refit_row<MODE, SH::PR>(part, row.bw, op.r, w_row, a.pool.lv, h, W);
+        sh.hrow[row.slice][row.r] = h;
+        if constexpr (MODE == Refit::DualAxis) sh.wrow[row.slice][row.r] = W;
     }
     if constexpr (MODE == Refit::RowAbsmax) {
         if (tid < DV) cc_out[tid] = 1.0f;
     }
     __syncthreads();
 
+    float gc[4];
     if constexpr (MODE == Refit::RowAbsmax) {
-        each_word<DV>(t, slice, [&](auto bw, const GroupRows &gr, int m) {
-            constexpr int B = decltype(bw)::value;
-            float Y[16];
-            gen_word_y<B, DIAG, DV>(w[m], sh.d, gr.x0, t.alpha, bc, Y);
-            word_scale<B>(Y, sh.hrow, gr.x0);
-            cw.store(tid + 256 * m, word_requant<B>(Y, cc));
-        });
-        return;
-    }
-
-    // pass 2: column maxima of |yh| per width
-    {
-        float mx[3][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        each_word<DV>(t, slice, [&](auto bw, const GroupRows &gr, int m) {
-            constexpr int B = decltype(bw)::value;
-            constexpr int K = B == 8 ? 0 : (B == 4 ? 1 : 2);
-            float Y[16];
-            gen_word_y<B, DIAG, DV>(w[m], sh.d, gr.x0, t.alpha, bc, Y);
 #pragma unroll
-            for (int s = 0; s < 8 / B; ++s) {
-                const float h = sh.hrow[gr.x0 + s];
+        for (int p = 0; p < NP; ++p) {
+            const float2 h = *reinterpret_cast<const float2 *>(&sh.hrow[slice][2 * p]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mx[K][e] = fmaxf(mx[K][e], fabsf(Y[4 * s + e] * h));
+            for (int e = 0; e < 4; ++e) {
+                Y[p][e] = Y[p][e] * h.x;
+                Y[p][4 + e] = Y[p][4 + e] * h.y;
             }
-        });
-        sh.u.cmax[slice][cg] = width_max(mx[0], mx[1], mx[2]);
-    }
-    __syncthreads();
-    if (tid < DV) refit_colmax<DV>(sh, tid);
-    __syncthreads();
-
-    // pass 3: fixed codes, least-squares sums
-    {
-        float ec[4];
-        ld4(&sh.ecol[4 * cg], ec);
-        float num[4] = {0.f, 0.f, 0.f, 0.f}, den[4] = {0.f, 0.f, 0.f, 0.f};
-        each_word<DV>(t, slice, [&](auto bw, const GroupRows &gr, int m) {
-            constexpr int B = decltype(bw)::value;
-            float Y[16];
-            gen_word_y<B, DIAG, DV>(w[m], sh.d, gr.x0, t.alpha, bc, Y);
-#pragma unroll
-            for (int s = 0; s < 8 / B; ++s) {
-                const float h = sh.hrow[gr.x0 + s];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Y[4 * s + e] *= h;
-            }
-            word_fit<B>(Y, sh.wrow, gr.x0, ec, num, den);
-        });
-        sh.d.red[0][slice][cg] = make_float4(num[0], num[1], num[2], num[3]);
-        sh.d.red[1][slice][cg] = make_float4(den[0], den[1], den[2], den[3]);
-    }
-    __syncthreads();
-    if (tid < DV) refit_colfit<DV>(sh, tid, cc_out);
-    __syncthreads();
-
-    // pass 4: requantize and store
-    float g[4];
-    ld4(&sh.gcol[4 * cg], g);
-    each_word<DV>(t, slice, [&](auto bw, const GroupRows &gr, int m) {
-        constexpr int B = decltype(bw)::value;
-        float Y[16];
-        gen_word_y<B, DIAG, DV>(w[m], sh.d, gr.x0, t.alpha, bc, Y);
-#pragma unroll
-        for (int s = 0; s < 8 / B; ++s) {
-            const float h = sh.hrow[gr.x0 + s];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) Y[4 * s + e] *= h;
         }
-        cw.store(tid + 256 * m, word_requant<B>(Y, g));
-    });
-}
-
-// ---- row-mix heads (kRowMix: 8- and 4-bit rows in any split, at most
-// kCompactPivots FP16 pivot rows, d = 128: the per-row maps of a row-unit
-// calibration).  The first half is the frozen row-mix body's (rowmix_sums:
-// both sums over rows on the matrix cores, here all four columns in one
-// pass: the register peak comes later).  Then, as in the uniform body, y
-// stays in registers through the four passes, indexed by word-step: Y[m]
-// holds word-step m's row (an 8-bit word) or the slot-0 row of its 4-bit
-// word, at most 64 values; the slot-1 row of a 4-bit word is formed again
-// from the packed word in each pass after the first.  The per-element
-// arithmetic is the generic body's (gen_word_y, word_fit, word_requant) in
-// the same order, so the two bodies give the same codes and scales.
-// The width of a word-step is a per-lane test (it differs between slices in
-// at most one word-step): measured faster than a uniform branch for the
-// word-steps wholly of one width.  Lanes past the head's last group (in the
-// last word-step) take no part in the sums and store nothing.
-
-// y of the 4 fields of view W (each at the top of its byte) of row slot x,
-// as gen_word_y forms it.
-template <bool DIAG>
-__device__ __forceinline__ void rm_row_y(uint32_t W, const DecodeShared<128> &d, int x, float al_w,
-                                         const float (&bc)[4], float *y)
-{
-    const float a_s = d.av[x];
-    const float al = DIAG ? d.al[x] : al_w;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = fmaf(al, sbyte(W, e), a_s * bc[e]);
-}
-
-// Calls f8(m, g) for word-step m of the thread if its group g = slice + 8 m
-// is 8-bit, or f4(m, g) if it is a 4-bit group that holds codes (g < ng),
-// for every m while 8 m < ng.
-template <class F8, class F4>
-__device__ __forceinline__ void rm_each_step(int slice, int g8, int ng, F8 &&f8, F4 &&f4)
-{
+        for (int e = 0; e < 4; ++e) gc[e] = cc[e];
+    } else {
+        // pass 2: yh = y r / r' and the column maxima per width
+        {
+            // the running maxima of one class fold into top[], divided by its
+            // q_b, where the next class begins
+            float mx[4] = {0.f, 0.f, 0.f, 0.f}, top[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-        if (8 * m >= ng) break;
-        const int g = slice + 8 * m;
-        if (g < g8) f8(m, g);
-        else if (g < ng) f4(m, g);
-    }
-}
-
-template <bool BF16, bool DIAG>
-__device__ __forceinline__ void refit_rowmix(const DecodeArgs &a, const TileCtx &t, RefitShared<128> &sh)
-{
-    constexpr Refit DA = Refit::DualAxis;
-    const int tid = threadIdx.x;
-    const int cg = tid & 31, slice = tid >> 5;
-    const int g8 = __builtin_amdgcn_readfirstlane(static_cast<int>(t.hi.g8));
-    const int ng = __builtin_amdgcn_readfirstlane(static_cast<int>(t.hi.groups));
-    float *rr_out = const_cast<float *>(t.rr);
-    float *cc_out = const_cast<float *>(t.cc);
-    // the buffer covers the codes region only (piv_off = 128 ng): words of
-    // groups past the head's last read 0
-    const CodeWords cw(t.codes, t.hi.piv_off);
-    uint32_t w[16];
+            for (int p = 0; p < NP; ++p) {
+                if (p == g.p4 || (HAS2 && p == g.p2 && g.p2 != g.p4)) {
+                    const float f = p == g.p4 ? 1.0f / 127.0f : 1.0f / 7.0f;
 #pragma unroll
-    for (int m = 0; m < 16; ++m) w[m] = 8 * m < ng ? cw.load(tid + 256 * m) : 0u;
-    PivotRegs<128, kCompactPivots> pr;
-    pivot_load<128, kCompactPivots>(t, slice, cg, pr);
-    const RowColOps op = load_ops<BF16, DIAG, 128>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
-    if (tid < 128) {
-        sh.ccol[tid] = op.c;
-        sh.wphys[tid] = a.pool.roww[t.h * 128 + tid];
-    }
-    rowmix_sums<DIAG, false, true>(a, t, sh.d, w, pr, op, g8, ng);
-
-    float bc[4], cc[4];
-    ld4(&sh.d.bcol[4 * cg], bc);
-    ld4(&sh.ccol[4 * cg], cc);
-    pivot_update<128, kCompactPivots>(t, slice, cg, pr, sh.d, bc);    // pivot rows take no part in the fits
-    const float al8 = t.alpha, al4 = t.alpha * (1.0f / 16.0f);
-
-    // pass 1: y on the old scales, the row partials (row slot g of an 8-bit
-    // group, 2 g - g8 and the next of a 4-bit one)
-    float Y[16][4];
-    rm_each_step(
-        slice, g8, ng,
-        [&](int m, int g) {
-            rm_row_y<DIAG>(w[m], sh.d, g, al8, bc, Y[m]);
-            put_row_partial<128, DA>(sh, g, cg, row_partial<DA>(Y[m], cc));
-        },
-        [&](int m, int g) {
-            const int x0 = 2 * g - g8;
-            float y1[4];
-            rm_row_y<DIAG>(slot_top<4>(w[m], 0), sh.d, x0, al4, bc, Y[m]);
-            rm_row_y<DIAG>(slot_top<4>(w[m], 1), sh.d, x0 + 1, al4, bc, y1);
-            put_row_partial<128, DA>(sh, x0, cg, row_partial<DA>(Y[m], cc));
-            put_row_partial<128, DA>(sh, x0 + 1, cg, row_partial<DA>(y1, cc));
-        });
-    __syncthreads();
-    if (tid < kSlotTable) {
-        int bw;
-        const int p = slot_row(t.hi, tid, bw);
-        if (p >= 0) {
-            refit_row<128, DA>(sh, tid, p, bw, sh.d.sr[p], rr_out, a.pool.lv);
-        } else {
-            sh.hrow[tid] = 0.f;
-            sh.wrow[tid] = 0.f;
-        }
-    }
-    __syncthreads();
-
-    // yh of the slot-1 row of the 4-bit word of word-step m, group g
-    auto slot1_yh = [&](int m, int g, float (&y1)[4]) {
-        const int x1 = 2 * g - g8 + 1;
-        rm_row_y<DIAG>(slot_top<4>(w[m], 1), sh.d, x1, al4, bc, y1);
-        const float h = sh.hrow[x1];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y1[e] *= h;
-    };
-
-    // pass 2: yh = y r / r' (in place for the kept rows) and the column
-    // maxima per width
-    {
-        float mx8[4] = {0.f, 0.f, 0.f, 0.f}, mx4[4] = {0.f, 0.f, 0.f, 0.f};
-        const float mx2[4] = {0.f, 0.f, 0.f, 0.f};
-        rm_each_step(
-            slice, g8, ng,
-            [&](int m, int g) {
-                const float h = sh.hrow[g];
+                    for (int e = 0; e < 4; ++e) {
+                        top[e] = fmaxf(top[e], mx[e] * f);
+                        mx[e] = 0.f;
+                    }
+                }
+                const float2 h = *reinterpret_cast<const float2 *>(&sh.hrow[slice][2 * p]);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    Y[m][e] *= h;
-                    mx8[e] = fmaxf(mx8[e], fabsf(Y[m][e]));
+                    Y[p][e] = Y[p][e] * h.x;
+                    Y[p][4 + e] = Y[p][4 + e] * h.y;
+                    mx[e] = max3_abs(mx[e], Y[p][e], Y[p][4 + e]);
                 }
-            },
-            [&](int m, int g) {
-                const float h = sh.hrow[2 * g - g8];
-                float y1[4];
-                slot1_yh(m, g, y1);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    Y[m][e] *= h;
-                    mx4[e] = fmaxf(mx4[e], fabsf(Y[m][e]));
-                    mx4[e] = fmaxf(mx4[e], fabsf(y1[e]));
-                }
-            });
-        sh.u.cmax[slice][cg] = width_max(mx8, mx4, mx2);
-    }
-    __syncthreads();
-    if (tid < 128) refit_colmax<128>(sh, tid);
-    __syncthreads();
+            }
+            const float f = HAS2 && g.p2 < g.pt ? 1.0f : (g.p4 < g.e4 ? 1.0f / 7.0f : 1.0f / 127.0f);
+            sh.u.cmax[slice][cg] = make_float4(fmaxf(top[0], mx[0] * f), fmaxf(top[1], mx[1] * f),
+                                               fmaxf(top[2], mx[2] * f), fmaxf(top[3], mx[3] * f));
+        }
+        __syncthreads();
+        if (tid < DV) refit_colmax<DV>(sh, tid);
+        __syncthreads();
 
-    // pass 3: fixed codes and the least-squares sums
-    {
-        float ec[4];
-        ld4(&sh.ecol[4 * cg], ec);
-        float num[4] = {0.f, 0.f, 0.f, 0.f}, den[4] = {0.f, 0.f, 0.f, 0.f};
-        rm_each_step(
-            slice, g8, ng, [&](int m, int g) { word_fit<8>(Y[m], sh.wrow, g, ec, num, den); },
-            [&](int m, int g) {
-                float y8[8];
-                slot1_yh(m, g, *reinterpret_cast<float(*)[4]>(&y8[4]));
+        // pass 3: fixed codes and the least-squares sums
+        {
+            float ec[4];
+            ld4(&sh.ecol[4 * cg], ec);
+            float num[4] = {0.f, 0.f, 0.f, 0.f}, den[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) y8[e] = Y[m][e];
-                word_fit<4>(y8, sh.wrow, 2 * g - g8, ec, num, den);
-            });
-        sh.d.red[0][slice][cg] = make_float4(num[0], num[1], num[2], num[3]);
-        sh.d.red[1][slice][cg] = make_float4(den[0], den[1], den[2], den[3]);
+            for (int p = 0; p < NP; ++p) {
+                const float2 W = *reinterpret_cast<const float2 *>(&sh.wrow[slice][2 * p]);
+                row_fit(&Y[p][0], W.x, ec, num, den);
+                row_fit(&Y[p][4], W.y, ec, num, den);
+            }
+            sh.d.red[0][slice][cg] = make_float4(num[0], num[1], num[2], num[3]);
+            sh.d.red[1][slice][cg] = make_float4(den[0], den[1], den[2], den[3]);
+        }
+        __syncthreads();
+        if (tid < DV) refit_colfit<DV>(sh, tid, cc_out);
+        __syncthreads();
+        ld4(&sh.gcol[4 * cg], gc);
     }
-    __syncthreads();
-    if (tid < 128) refit_colfit<128>(sh, tid, cc_out);
-    __syncthreads();
 
     // pass 4: requantize on the new scales, store in place
-    float gc[4];
-    ld4(&sh.gcol[4 * cg], gc);
-    rm_each_step(
-        slice, g8, ng, [&](int m, int) { cw.store(tid + 256 * m, word_requant<8>(Y[m], gc)); },
-        [&](int m, int g) {
-            float y8[8];
-            slot1_yh(m, g, *reinterpret_cast<float(*)[4]>(&y8[4]));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y8[e] = Y[m][e];
-            cw.store(tid + 256 * m, word_requant<4>(y8, gc));
-        });
+    for (int p = 0; p < NP; ++p) {
+        if (p < g.p4) {
+            cw.st8(2 * p, requant_rows<8, 1>(&Y[p][0], gc) ^ 0x80808080u);
+            cw.st8(2 * p + 1, requant_rows<8, 1>(&Y[p][4], gc) ^ 0x80808080u);
+        } else if (p < g.e4) {
+            cw.st4(p - g.p4, requant_rows<4, 2>(&Y[p][0], gc) ^ 0x88888888u);
+        } else if (HAS2 && (p & 1) == 0 && p >= g.p2 && p < g.pt) {
+            const uint32_t P = requant_rows<2, 2>(&Y[p][0], gc) |
+                               (requant_rows<2, 2>(&Y[p + 1 < NP ? p + 1 : p][0], gc) << 4);
+            cw.st2((p - g.p2) >> 1, P ^ 0xAAAAAAAAu);
+        }
+    }
 }
 
 // A tile of uniform layout L: codes (1024 bytes per word-step), then r, c.
@@ -826,10 +763,19 @@ __device__ __forceinline__ void run_refit_uniform_piv(const DecodeArgs &a, TileC
     refit_uniform<BF16, DIAG, u.m8, u.m4, u.m2, MODE, true>(a, t, sh);
 }
 
-template <int DV, bool BF16, int LAYOUT, bool DIAG, Refit MODE>
-__global__ __launch_bounds__(256) void refit_kernel(DecodeArgs a)
+// NP: the row pairs of the slot bodies (layouts 0 and kRowMix; 0 for the
+// compiled layouts).
+// The slot bodies' second bound is the waves per SIMD that their 8 NP values
+// leave room for; without it the compiler takes a few registers more than the
+// next step of occupancy.
+constexpr int refit_waves(int np) { return np == 0 ? 1 : (np <= 6 ? 5 : (np <= 10 ? 4 : 3)); }
+
+template <int DV, bool BF16, int LAYOUT, bool DIAG, Refit MODE, int NP = 0>
+__global__ __launch_bounds__(256, refit_waves(NP)) void refit_kernel(DecodeArgs a)
 {
-    __shared__ RefitShared<DV> sh;
+    constexpr bool ROWMIX = LAYOUT == kRowMix;
+    using Shared = typename std::conditional<NP == 0, RefitShared<128>, SlotRefitShared<DV, NP == 0 ? 1 : NP, ROWMIX>>::type;
+    __shared__ Shared sh;
     const PoolView &P = a.pool;
     TileCtx t;
     uint32_t tile_bytes = 0;
@@ -868,32 +814,52 @@ __global__ __launch_bounds__(256) void refit_kernel(DecodeArgs a)
         t.codes = reinterpret_cast<uint32_t *>(rec);
         t.rr = reinterpret_cast<const float *>(rec + t.hi.r_off);
         t.cc = t.rr + P.dk;
-        if constexpr (DV == 128 && LAYOUT == kRowMix) {
-            static_assert(MODE == Refit::DualAxis, "the row-mix refitting body runs the dual-axis fit");
-            refit_rowmix<BF16, DIAG>(a, t, sh);
-        } else {
-            refit_generic<BF16, DIAG, DV, MODE>(a, t, sh);
+        refit_slots<BF16, DIAG, DV, NP, !ROWMIX, ROWMIX ? kCompactPivots : kMaxPivots, MODE, ROWMIX>(a, t, sh);
+    }
+}
+
+// Heads of any mix at the compiled pair count that holds the launch's
+// largest head.
+template <bool BF16, bool DIAG, Refit MODE>
+hipError_t launch_refit_slots(const DecodeArgs &a, unsigned grid, hipStream_t s)
+{
+    const int np = slot_pairs_compiled(a.pairs, a.pool.dv);
+    if (a.pool.dv == 64) {
+        switch (np) {
+        case 4: hipLaunchKernelGGL((refit_kernel<64, BF16, 0, DIAG, MODE, 4>), dim3(grid), dim3(256), 0, s, a); break;
+        case 6: hipLaunchKernelGGL((refit_kernel<64, BF16, 0, DIAG, MODE, 6>), dim3(grid), dim3(256), 0, s, a); break;
+        default:
+            hipLaunchKernelGGL((refit_kernel<64, BF16, 0, DIAG, MODE, kSlotPairs64>), dim3(grid), dim3(256), 0, s, a);
+            break;
+        }
+    } else {
+        switch (np) {
+        case 6: hipLaunchKernelGGL((refit_kernel<128, BF16, 0, DIAG, MODE, 6>), dim3(grid), dim3(256), 0, s, a); break;
+        case 8: hipLaunchKernelGGL((refit_kernel<128, BF16, 0, DIAG, MODE, 8>), dim3(grid), dim3(256), 0, s, a); break;
+        case 10: hipLaunchKernelGGL((refit_kernel<128, BF16, 0, DIAG, MODE, 10>), dim3(grid), dim3(256), 0, s, a); break;
+        default:
+            hipLaunchKernelGGL((refit_kernel<128, BF16, 0, DIAG, MODE, kSlotPairsAny>), dim3(grid), dim3(256), 0, s, a);
+            break;
         }
     }
+    return hipGetLastError();
 }
 
 template <bool BF16, bool DIAG, Refit MODE>
 hipError_t launch_refit_any(const DecodeArgs &a, int layout, unsigned grid, hipStream_t s)
 {
-    if constexpr (MODE == Refit::RowAbsmax) {
-        // uniform layouts are launched on the lean body (launch_decode_rowmax)
-        if (a.pool.dv == 128) hipLaunchKernelGGL((refit_kernel<128, BF16, 0, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((refit_kernel<64, BF16, 0, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a);
-    } else if (a.pool.dv == 128) {
-        switch (layout) {
+    if (a.pool.dv == 128 && layout == kRowMix) {
+        hipLaunchKernelGGL((refit_kernel<128, BF16, kRowMix, DIAG, MODE, kSlotPairs84>), dim3(grid), dim3(256), 0, s, a);
+        return hipGetLastError();
+    }
+    if constexpr (MODE == Refit::DualAxis) {
+        // (in the row-absmax step uniform layouts are launched on the lean body, launch_decode_rowmax)
+        switch (a.pool.dv == 128 ? layout : 0) {
         case 1: hipLaunchKernelGGL((refit_kernel<128, BF16, 1, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a); break;
         case 2: hipLaunchKernelGGL((refit_kernel<128, BF16, 2, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a); break;
         case 3: hipLaunchKernelGGL((refit_kernel<128, BF16, 3, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a); break;
         case 4: hipLaunchKernelGGL((refit_kernel<128, BF16, 4, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a); break;
         case 5: hipLaunchKernelGGL((refit_kernel<128, BF16, 5, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a); break;
-        case kRowMix:
-            hipLaunchKernelGGL((refit_kernel<128, BF16, kRowMix, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a);
-            break;
         case kMultiUniform:
             hipLaunchKernelGGL((refit_kernel<128, BF16, kMultiUniform, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a);
             break;
@@ -918,12 +884,11 @@ hipError_t launch_refit_any(const DecodeArgs &a, int layout, unsigned grid, hipS
         case kMixedPivotBase + 2:
             hipLaunchKernelGGL((refit_kernel<128, BF16, kMixedPivotBase + 2, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a);
             break;
-        default: hipLaunchKernelGGL((refit_kernel<128, BF16, 0, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a); break;
+        default: return launch_refit_slots<BF16, DIAG, MODE>(a, grid, s);
         }
-    } else {
-        hipLaunchKernelGGL((refit_kernel<64, BF16, 0, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a);
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    return launch_refit_slots<BF16, DIAG, MODE>(a, grid, s);
 }
 
 template <Refit MODE>

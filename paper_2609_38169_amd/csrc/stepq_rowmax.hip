@@ -56,17 +56,6 @@ __device__ __forceinline__ void column_sums_rowmax(const DecodeArgs &a, int tile
     __syncthreads();
 }
 
-// max(|a|, |b|, |c|) in one instruction.  Written out because the
-// compiler's own form would first quiet each input (the values come from
-// inline assembly, which it cannot prove free of signalling NaNs); finite
-// values only reach it here.
-__device__ __forceinline__ float max3_abs(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 // z of thread row r, column e, from the row-pair registers.
 template <bool DIAG>
 __device__ __forceinline__ float row_z(uint32_t hp, int half, float coef, float a_s, float delta)

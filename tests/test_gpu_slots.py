@@ -1,0 +1,99 @@
+"""GPU parity of the bodies for heads of any row-width mix (rows held in pairs
+of row slots), against the fp64 oracle through the C ABI: at each compiled
+pair count the splits that fill it, single rows, class boundaries inside a
+round of slices, empty 4- and 2-bit slots and many FP16 pivot rows, in every
+scale mode."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_38169_amd import stepq
+import _parity as PT
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0)
+
+# (d_k, d_v): heads as (8-bit, 4-bit, 2-bit, FP16 rows)
+SHAPES = {
+    "dv64-4pairs": (32, 64, [(17, 13, 2, 0), (1, 30, 1, 0), (0, 0, 32, 0), (32, 0, 0, 0), (5, 3, 20, 4)]),
+    "dv64-6pairs": (96, 64, [(33, 33, 30, 0), (17, 31, 48, 0), (96, 0, 0, 0), (0, 96, 0, 0), (31, 16, 17, 32)]),
+    "dv64-8pairs": (128, 64, [(33, 1, 94, 0), (17, 33, 78, 0), (65, 63, 0, 0), (1, 1, 126, 0), (50, 30, 20, 28)]),
+    "dv64-1row": (1, 64, [(1, 0, 0, 0), (0, 1, 0, 0), (0, 0, 1, 0), (0, 0, 0, 1)]),
+    "dv128-6pairs": (37, 128, [(9, 17, 11, 0), (1, 1, 35, 0), (37, 0, 0, 0), (0, 33, 4, 0), (7, 5, 1, 24)]),
+    "dv128-8pairs": (77, 128, [(25, 31, 21, 0), (9, 17, 51, 0), (0, 77, 0, 0), (45, 0, 0, 32)]),
+    "dv128-10pairs": (120, 128, [(41, 33, 46, 0), (25, 17, 78, 0), (119, 1, 0, 0), (30, 44, 26, 20)]),
+    "dv128-12pairs": (128, 128, [(33, 17, 78, 0), (17, 33, 78, 0), (49, 18, 61, 0), (64, 48, 0, 16), (30, 20, 46, 32)]),
+}
+
+
+def _bits(rng, dk, heads):
+    return np.stack([rng.permutation(np.repeat(np.array([8, 4, 2, 16], np.uint8), h)) for h in heads])
+
+
+@pytest.mark.parametrize("mode", [False, True, "row_absmax"])
+@pytest.mark.parametrize("act,kda", [("f32", False), ("bf16", True)])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_slot_bodies_one_step(shape, act, kda, mode):
+    dk, dv, heads = SHAPES[shape]
+    print(f"slot bodies {shape} act={act} kda={kda} mode={mode}", flush=True)
+    rng = np.random.default_rng(len(shape) * 1000 + dk)
+    bits = _bits(rng, dk, heads)
+    Hv, n_slots, B = len(heads), 3, 2
+    S = (rng.standard_normal((n_slots, Hv, dk, dv)) * 0.05).astype(np.float32)
+    tb = np.broadcast_to(bits[None], (n_slots,) + bits.shape).reshape(-1, dk)
+    r, c = oracle.fit_absmax(S.reshape(-1, dk, dv), bits=tb)
+    c = np.where(c > 0, c, 1.0)
+    codes, pv = oracle.quantize(S.reshape(-1, dk, dv).astype(np.float64), r, c, tb)
+    pool = stepq.Pool(n_slots, Hv, Hv, dk, dv, bits, device=DEV)
+    all_ids = torch.arange(n_slots, dtype=torch.int32, device=DEV)
+    up = lambda a, *s: torch.from_numpy(np.ascontiguousarray(a.reshape(*s))).to(DEV)
+    pool.import_(all_ids, up(codes, n_slots, Hv, dk, dv), up(r.astype(np.float32), n_slots, Hv, dk),
+                 up(c.astype(np.float32), n_slots, Hv, dv))
+    pool.import_pivots(all_ids, up(pv.view(np.int16), n_slots, Hv, dk, dv))
+    wrow = np.exp(0.3 * rng.standard_normal((Hv, dk))).astype(np.float32)
+    pool.set_row_weight(wrow)
+    sel = rng.permutation(n_slots)[:B].astype(np.int32)
+    q = rng.standard_normal((B, Hv, dk)); q /= np.linalg.norm(q, axis=-1, keepdims=True)
+    k = rng.standard_normal((B, Hv, dk)); k /= np.linalg.norm(k, axis=-1, keepdims=True)
+    v = rng.standard_normal((B, Hv, dv))
+    gate = rng.uniform(0.5, 1.0, (B, Hv, dk)) if kda else rng.uniform(0.9, 1.0, (B, Hv))
+    be = rng.uniform(0, 1, (B, Hv))
+    dt = torch.bfloat16 if act == "bf16" else torch.float32
+    dev_in = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dt) for a in (q, k, v, gate, be)]
+    q, k, v, gate, be = (t.float().numpy().astype(np.float64) for t in dev_in)
+    o = torch.empty((B, Hv, dv), dtype=torch.float32, device=DEV)
+    step = pool.step_kda if kda else pool.step
+    step(torch.from_numpy(sel).to(DEV), *(t.to(DEV) for t in dev_in), o, refit=mode)
+    g_codes = torch.empty((n_slots, Hv, dk, dv), dtype=torch.int8, device=DEV)
+    g_pv = torch.empty((n_slots, Hv, dk, dv), dtype=torch.int16, device=DEV)
+    g_r, g_c = torch.empty((n_slots, Hv, dk), device=DEV), torch.empty((n_slots, Hv, dv), device=DEV)
+    pool.export(all_ids, g_codes, g_r, g_c)
+    pool.export_pivots(all_ids, g_pv)
+    torch.cuda.synchronize()
+    got = g_codes.cpu().numpy().reshape(-1, dk, dv)
+    gpv = g_pv.cpu().numpy().view(np.uint16).reshape(-1, dk, dv)
+    gr, gc = g_r.cpu().numpy().reshape(-1, dk), g_c.cpu().numpy().reshape(-1, dv)
+    tiles = (sel[:, None] * Hv + np.arange(Hv)[None]).reshape(-1)
+    args = (codes[tiles], r[tiles], c[tiles], tb[tiles], q.reshape(-1, dk), k.reshape(-1, dk), v.reshape(-1, dv),
+            gate.reshape((-1, dk) if kda else (-1,)), be.reshape(-1))
+    if mode is True:
+        wt = np.broadcast_to(wrow[None].astype(np.float64), (B, Hv, dk)).reshape(-1, dk)
+        new, rn, cn, o_ref, ex, npv = oracle.decode_step_refit(*args, w=wt, want=("y", "c_range"),
+                                                               tie_window=PT.TIE_WINDOW, pv=pv[tiles])
+        PT.compare_refit(got[tiles], gr[tiles], gc[tiles], new, rn, cn, ex["y"], ex["c_range"], tb[tiles], shape)
+        y = ex["y"]
+    elif mode == "row_absmax":
+        new, rn, cn, o_ref, y, npv = oracle.decode_step_rowmax(*args, want_y=True, pv=pv[tiles])
+        ones = np.ones(cn.shape)
+        PT.compare_refit(got[tiles], gr[tiles], gc[tiles], new, rn, cn, y, (ones, ones), tb[tiles], shape)
+    else:
+        new, o_ref, y, npv = oracle.decode_step(*args, want_y=True, pv=pv[tiles])
+        PT.compare_codes(got[tiles], new, y, shape)
+        assert np.array_equal(gr[tiles], r[tiles]) and np.array_equal(gc[tiles], c[tiles])
+    PT.compare_pivots(gpv[tiles], npv, y, tb[tiles] == 16, shape)
+    PT.compare_out(o.cpu().numpy().reshape(-1, dv), o_ref)
+    rest = np.setdiff1d(np.arange(n_slots), sel)
+    rt = (rest[:, None] * Hv + np.arange(Hv)[None]).reshape(-1)
+    assert np.array_equal(got[rt], codes[rt]) and np.array_equal(gpv[rt], pv[rt])
+    assert np.array_equal(gr[rt], r[rt]) and np.array_equal(gc[rt], c[rt])

@@ -442,3 +442,15 @@ def test_pool_plan_launch_counts():
     assert len(refit) == 2 and sum(n for _, _, n in refit) == w.n_v_heads
     with pytest.raises(stepq.StepqError):
         stepq.stepq_pool_plan(1, 2, 1, 128, 128, np.full((2, 128), 6, np.uint8))
+
+
+@pytest.mark.parametrize("dk,dv", [(128, 128), (128, 64), (96, 64), (77, 128)])
+def test_pool_plan_accepts_every_width_split(dk, dv):
+    """Every split of the rows into 8-, 4- and 2-bit rows fits the row pairs
+    of the compiled bodies: the plan check, which refuses a head with more,
+    accepts pools whose heads run through all splits."""
+    for n8 in range(dk + 1):
+        bits = np.stack([np.repeat(np.array([8, 4, 2], np.uint8), (n8, n4, dk - n8 - n4)) for n4 in range(dk - n8 + 1)])
+        H = len(bits)
+        launches, order = stepq.stepq_pool_plan(1, H, H, dk, dv, bits)
+        assert sorted(order.tolist()) == list(range(H))
