@@ -23,9 +23,6 @@
 // the generic bodies accumulate them with v_fma_mix.  Per-column partial
 // sums of the 8 threads that share a column meet in LDS; one pass over the
 // words kept in registers then rewrites the codes in place.
-//
-// tile_kernel: pack (from fp32 states or raw codes), unpack and dequantize
-// whole tiles; not on the decode path.
 #include "stepq_device.h"
 
 namespace stepq {
@@ -386,113 +383,6 @@ __global__ __launch_bounds__(256) void stream_ref_kernel(DecodeArgs a, uint32_t 
     if (tid < P.dv) a.o[static_cast<size_t>(t.tile) * P.dv + tid] = acc * __uint_as_float(zero);
 }
 
-template <TileOp OP>
-__global__ __launch_bounds__(256) void tile_kernel(TileArgs a)
-{
-    const PoolView &P = a.pool;
-    const int tid = threadIdx.x;
-    const int tile = blockIdx.x;
-    const int n_i = tile / P.Hv;
-    const int h = tile - n_i * P.Hv;
-    const HeadInfo hi = P.heads[h];
-    const int slot = a.slot_ids[n_i];
-    uint8_t *rec = P.base + static_cast<uint64_t>(slot) * P.slot_bytes + hi.tile_off;
-    uint32_t *codes = reinterpret_cast<uint32_t *>(rec);
-    float *rr = reinterpret_cast<float *>(rec + hi.r_off);
-    float *cc = rr + P.dk;
-    const uint8_t *perm = P.perm + h * P.dk;
-    const int dk = P.dk, dv = P.dv, CG = dv / 4;
-    const size_t tdk = static_cast<size_t>(tile) * dk, tdv = static_cast<size_t>(tile) * dv;
-
-    if constexpr (OP == TileOp::Load || OP == TileOp::Import) {
-        for (int p = tid; p < dk; p += 256) rr[p] = a.r_in[tdk + perm[p]];
-        for (int j = tid; j < dv; j += 256) cc[j] = a.c_in[tdv + j];
-        // zero padding: end of the codes region and end of the record
-        uint32_t *rec32 = reinterpret_cast<uint32_t *>(rec);
-        for (uint32_t d = hi.groups * CG + tid; d < hi.piv_off / 4; d += 256) rec32[d] = 0u;
-        for (uint32_t d = (hi.r_off + 4u * (dk + dv)) / 4 + tid; d < hi.tile_bytes / 4; d += 256) rec32[d] = 0u;
-    }
-    if constexpr (OP == TileOp::Export) {
-        for (int p = tid; p < dk; p += 256) a.r_out[tdk + perm[p]] = rr[p];
-        for (int j = tid; j < dv; j += 256) a.c_out[tdv + j] = cc[j];
-    }
-
-    // FP16 pivot rows: physical rows 0 .. n16-1, d_v binary16 values each
-    uint16_t *piv = reinterpret_cast<uint16_t *>(rec + hi.piv_off);
-    const int npv = static_cast<int>(hi.n16) * dv;
-    if constexpr (OP == TileOp::ExportPivots || OP == TileOp::ImportPivots) {
-        for (int e = tid; e < dk * dv; e += 256) {
-            const int p = e / dv, j = e - p * dv;
-            const size_t o = (tdk + perm[p]) * dv + j;
-            if constexpr (OP == TileOp::ExportPivots) a.piv_out[o] = p < hi.n16 ? piv[e] : static_cast<uint16_t>(0);
-            else if (p < hi.n16) piv[e] = a.piv_in[o];
-        }
-        return;
-    } else {
-        for (int e = tid; e < npv; e += 256) {
-            const int p = e / dv, j = e - p * dv;
-            const size_t o = (tdk + perm[p]) * dv + j;
-            if constexpr (OP == TileOp::Load)
-                piv[e] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(a.state[o]));    // nearest even
-            else if constexpr (OP == TileOp::Export)
-                a.codes_out[o] = 0;
-            else if constexpr (OP == TileOp::Dequant)
-                a.deq_out[o] = static_cast<float>(__builtin_bit_cast(_Float16, piv[e]));
-        }
-    }
-
-    const int nw = static_cast<int>(hi.groups) * CG;
-    for (int d = tid; d < nw; d += 256) {
-        const int g = d / CG;
-        const int j0 = 4 * (d - g * CG);
-        const GroupRows gr = group_rows(hi, g);
-        const int B = gr.bits;
-        const int qbi = (1 << (B - 1)) - 1;
-        const float iq = P.lv.iq[B == 8 ? 0 : (B == 4 ? 1 : 2)];     // q = level * iq
-        const uint32_t fmask = (1u << B) - 1u;
-        if constexpr (OP == TileOp::Load || OP == TileOp::Import) {
-            uint32_t word = 0;
-            for (int s = 0; s < gr.nslot; ++s) {
-                const int p = gr.p0 + s;
-                if (p >= gr.pend) break;
-                const int i = perm[p];
-                for (int e = 0; e < 4; ++e) {
-                    const int j = j0 + e;
-                    int code;
-                    if constexpr (OP == TileOp::Load) {
-                        const float x = a.state[(tdk + i) * dv + j];
-                        const float rc = a.r_in[tdk + i] * a.c_in[tdv + j];
-                        float y = __builtin_rintf((x * iq) / rc);
-                        y = fminf(fmaxf(y, -static_cast<float>(qbi)), static_cast<float>(qbi));
-                        code = static_cast<int>(y);
-                    } else {
-                        code = a.codes_in[(tdk + i) * dv + j];
-                    }
-                    word |= (static_cast<uint32_t>(code) & fmask) << (8 * e + s * B);
-                }
-            }
-            codes[d] = word;
-        } else {
-            const uint32_t word = codes[d];
-            for (int s = 0; s < gr.nslot; ++s) {
-                const int p = gr.p0 + s;
-                if (p >= gr.pend) break;
-                const int i = perm[p];
-                for (int e = 0; e < 4; ++e) {
-                    const int j = j0 + e;
-                    int f = static_cast<int>((word >> (8 * e + s * B)) & fmask);
-                    if (f > qbi) f -= (1 << B);
-                    if constexpr (OP == TileOp::Export) {
-                        a.codes_out[(tdk + i) * dv + j] = static_cast<int8_t>(f);
-                    } else {
-                        a.deq_out[(tdk + i) * dv + j] = (rr[p] * cc[j]) * (static_cast<float>(f) / iq);
-                    }
-                }
-            }
-        }
-    }
-}
-
 template <bool BF16, bool DIAG>
 hipError_t launch_decode_128(const DecodeArgs &a, int layout, unsigned grid, hipStream_t s)
 {
@@ -581,25 +471,6 @@ hipError_t launch_stream_ref(const DecodeArgs &a, bool bf16, hipStream_t stream)
     if (grid == 0) return hipSuccess;
     if (bf16) hipLaunchKernelGGL(stream_ref_kernel<true>, dim3(grid), dim3(256), 0, stream, a, 0u);
     else hipLaunchKernelGGL(stream_ref_kernel<false>, dim3(grid), dim3(256), 0, stream, a, 0u);
-    return hipGetLastError();
-}
-
-hipError_t launch_tile_op(const TileArgs &a, TileOp op, hipStream_t stream)
-{
-    const unsigned grid = static_cast<unsigned>(a.n) * static_cast<unsigned>(a.pool.Hv);
-    if (grid == 0) return hipSuccess;
-    switch (op) {
-    case TileOp::Load: hipLaunchKernelGGL(tile_kernel<TileOp::Load>, dim3(grid), dim3(256), 0, stream, a); break;
-    case TileOp::Import: hipLaunchKernelGGL(tile_kernel<TileOp::Import>, dim3(grid), dim3(256), 0, stream, a); break;
-    case TileOp::Export: hipLaunchKernelGGL(tile_kernel<TileOp::Export>, dim3(grid), dim3(256), 0, stream, a); break;
-    case TileOp::Dequant: hipLaunchKernelGGL(tile_kernel<TileOp::Dequant>, dim3(grid), dim3(256), 0, stream, a); break;
-    case TileOp::ExportPivots:
-        hipLaunchKernelGGL(tile_kernel<TileOp::ExportPivots>, dim3(grid), dim3(256), 0, stream, a);
-        break;
-    case TileOp::ImportPivots:
-        hipLaunchKernelGGL(tile_kernel<TileOp::ImportPivots>, dim3(grid), dim3(256), 0, stream, a);
-        break;
-    }
     return hipGetLastError();
 }
 
