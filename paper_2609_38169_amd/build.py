@@ -13,6 +13,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -35,12 +36,25 @@ HIP_FLAGS = [
     "-Wall", "-Wno-unused-function",
 ]
 CXX_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-pthread"]
+# the binding's native argument checks: a Python module against torch's headers
+ARGS_SOURCE = "stepq_args.cpp"
+ARGS_MODULE = os.path.join(HERE, "_stepq_args.so")
 
 
 def device_targets(path: str) -> list[str]:
     """Offload targets named in a built library's device bundle."""
     data = open(path, "rb").read()
     return sorted(set(t.decode() for t in re.findall(rb"hipv4-amdgcn-amd-amdhsa--(gfx[0-9a-f]+)", data)))
+
+
+def args_command(out: str, csrc: str) -> list[str]:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = [f for d in include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+           for f in ("-I", d)]
+    return (["g++"] + CXX_FLAGS + ["-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}"] + inc
+            + [os.path.join(csrc, ARGS_SOURCE), "-o", out, "-L", tlib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"])
 
 
 def build(extra_flags: list[str] | None = None, out: str = LIB, verbose: bool = False, csrc: str = CSRC,
@@ -69,6 +83,8 @@ def build(extra_flags: list[str] | None = None, out: str = LIB, verbose: bool = 
         o = os.path.join(build_dir, s + ".o")
         cmds.append(["g++"] + CXX_FLAGS + inc + ["-c", os.path.join(csrc, s), "-o", o])
         objs.append(o)
+    if out == LIB:
+        cmds.append(args_command(ARGS_MODULE + ".tmp", csrc))
     # the translation units are independent: compile them side by side
     with ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as ex:
         for f in [ex.submit(run, c) for c in cmds]:
@@ -81,6 +97,8 @@ def build(extra_flags: list[str] | None = None, out: str = LIB, verbose: bool = 
         os.remove(tmp)
         raise RuntimeError(f"libstepq device bundle targets {targets}, expected only {ARCH}")
     os.replace(tmp, out)
+    if out == LIB:
+        os.replace(ARGS_MODULE + ".tmp", ARGS_MODULE)
     return out
 
 

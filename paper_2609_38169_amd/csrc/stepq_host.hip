@@ -29,6 +29,10 @@ struct stepq_pool {
     int levels = STEPQ_LEVELS_ABSMAX; // level normalisation of the codes
     stepq::LaunchPlan plan;           // the decode launches of a step (stepq_plan.h)
     stepq::LaunchHead *d_head_order = nullptr;  // plan.order on the device
+    // what every launch passes, formed once the tables are allocated
+    stepq::PoolView view;
+    stepq::FastDiv div_hv;                      // divide by Hv
+    std::vector<stepq::FastDiv> div_cls;        // divide by the heads of each class
 };
 
 namespace {
@@ -57,7 +61,7 @@ stepq_status build_layout(const stepq_pool_desc *d, std::vector<HeadInfo> *heads
 
 using stepq::fast_div;
 
-stepq::PoolView view(const stepq_pool *p)
+stepq::PoolView make_view(const stepq_pool *p)
 {
     stepq::PoolView v;
     v.base = p->mem;
@@ -264,6 +268,9 @@ stepq_status stepq_pool_create(const stepq_pool_desc *desc, void *device_mem, si
         return fail(e == hipErrorOutOfMemory ? STEPQ_E_NOMEM : STEPQ_E_HIP,
                     std::string("layout tables: ") + hipGetErrorString(e));
     }
+    p->view = make_view(p);
+    p->div_hv = fast_div(static_cast<uint32_t>(p->Hv));
+    for (int n : p->plan.cls_cnt) p->div_cls.push_back(fast_div(static_cast<uint32_t>(n)));
     *out = p;
     return STEPQ_OK;
 }
@@ -321,7 +328,7 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
     st = check_slots(p, slot_ids, batch, s);
     if (st != STEPQ_OK) return st;
     stepq::DecodeArgs a;
-    a.pool = view(p);
+    a.pool = p->view;
     a.slot_ids = slot_ids;
     a.q = q;
     a.k = k;
@@ -358,12 +365,12 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
         // one launch of the refitting bodies
         a.head_list = p->d_head_order;
         a.n_heads = p->Hv;
-        a.div_heads = fast_div(static_cast<uint32_t>(p->Hv));
+        a.div_heads = p->div_hv;
         e = launch(plan.mixed_code);
     } else if (plan.cls_code.empty()) {
         a.head_list = nullptr;
         a.n_heads = p->Hv;
-        a.div_heads = fast_div(static_cast<uint32_t>(p->Hv));
+        a.div_heads = p->div_hv;
         e = launch(plan.layout);
     } else {
         // a mixed pool: one launch per layout class, each with its own register budget
@@ -371,7 +378,7 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
             a.head_list = p->d_head_order + plan.cls_off[c];
             a.n_heads = plan.cls_cnt[c];
             a.pairs = plan.cls_pairs[c];
-            a.div_heads = fast_div(static_cast<uint32_t>(plan.cls_cnt[c]));
+            a.div_heads = p->div_cls[c];
             e = launch(plan.cls_code[c]);
         }
     }
@@ -414,7 +421,7 @@ stepq_status stepq_decode_stream_ref(stepq_pool *p, const int32_t *slot_ids, int
     st = check_slots(p, slot_ids, batch, s);
     if (st != STEPQ_OK) return st;
     stepq::DecodeArgs a{};
-    a.pool = view(p);
+    a.pool = p->view;
     a.slot_ids = slot_ids;
     a.q = q;
     a.k = k;
@@ -427,7 +434,7 @@ stepq_status stepq_decode_stream_ref(stepq_pool *p, const int32_t *slot_ids, int
     // one launch over every head, in the order of the combined decode launch
     a.head_list = p->plan.order.empty() ? nullptr : p->d_head_order;
     a.n_heads = p->Hv;
-    a.div_heads = fast_div(static_cast<uint32_t>(p->Hv));
+    a.div_heads = p->div_hv;
     const hipError_t e = stepq::launch_stream_ref(a, act_dtype == STEPQ_BF16, s);
     return e == hipSuccess ? STEPQ_OK : hip_fail(e, "reference launch");
 }
@@ -438,7 +445,7 @@ static stepq_status tile_op(const stepq_pool *p, const int32_t *ids, int32_t n, 
     auto s = static_cast<hipStream_t>(stream);
     stepq_status st = check_slots(p, ids, n, s);
     if (st != STEPQ_OK) return st;
-    a.pool = view(p);
+    a.pool = p->view;
     a.slot_ids = ids;
     a.n = n;
     hipError_t e = stepq::launch_tile_op(a, op, s);

@@ -11,7 +11,8 @@
 // caller's base pointers need only their element's alignment: accesses to
 // them are typed so.  Against the earlier one-word, one-dword-per-access form:
 // pack of 64 requests x 32 heads 41.4 -> 32.5 us, export + import with FP16
-// rows of 32 requests x 32 heads 72.1 -> 35.2 us.
+// rows of 32 requests x 32 heads 72.1 -> 35.2 us (four calls; the host's share is
+// in stepq_args.cpp).
 #include "stepq_device.h"
 
 namespace stepq {

@@ -53,11 +53,12 @@ class stepq_pool_desc(ctypes.Structure):
 
 
 _lib = None
+_native = None      # the _stepq_args module, bound to the library's calls by lib()
 
 
 def lib():
     """The loaded library.  Raises if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: build it with paper_2609_38169_amd.build.build()")
@@ -99,6 +100,11 @@ def lib():
             fn = getattr(L, name)
             fn.argtypes = args
             fn.restype = res
+        from . import _stepq_args
+        _stepq_args.bind(*(ctypes.cast(getattr(L, name), P).value for name in (
+            "stepq_decode_step_ex", "stepq_pool_load", "stepq_pool_import", "stepq_pool_export", "stepq_pool_dequant",
+            "stepq_pool_export_pivots", "stepq_pool_import_pivots")), torch._C._cuda_getCurrentRawStream)
+        _native = _stepq_args
         _lib = L
     return _lib
 
@@ -163,6 +169,8 @@ def stepq_pool_plan(n_slots, n_v_heads, n_qk_heads, d_k, d_v, row_bits, levels=S
 class Pool:
     """A state pool whose memory is a torch uint8 tensor on the current device."""
 
+    _plain = None
+
     def __init__(self, n_slots, n_v_heads, n_qk_heads, d_k, d_v, row_bits, device=None,
                  levels=STEPQ_LEVELS_ABSMAX):
         self.device = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
@@ -180,8 +188,12 @@ class Pool:
             _check(lib().stepq_pool_create(ctypes.byref(d), ctypes.c_void_p(self.memory.data_ptr()),
                                            self.pool_bytes, ctypes.byref(h)))
         self.handle = h
+        # what the native checks compare with (a device without an index matches no tensor, as in _dev)
+        index = -1 if self.device.index is None else self.device.index
+        self._plain = _native.plain(h.value, index, n_v_heads, n_qk_heads, d_k, d_v)
 
     def close(self):
+        self._plain = None
         if getattr(self, "handle", None):
             with torch.cuda.device(self.device):
                 lib().stepq_pool_destroy(self.handle)
@@ -201,7 +213,7 @@ class Pool:
     # (the single-axis INT-b baseline); adjacent: the STEPQ_STEP_ADJACENT_SLOTS
     # hint (slot_ids[b] = slot_ids[0] + b)
     def step(self, slot_ids, q, k, v, alpha, beta, o, stream=None, refit=False, adjacent=False):
-        flags = _refit_flags(refit) | (STEPQ_STEP_ADJACENT_SLOTS if adjacent else 0)
+        flags = (_refit_flags(refit) if refit is not False else 0) | (STEPQ_STEP_ADJACENT_SLOTS if adjacent else 0)
         if flags:
             stepq_decode_step_ex(self, slot_ids, q, k, v, alpha, beta, o, flags, stream)
         else:
@@ -293,7 +305,16 @@ def _ids(pool: Pool, slot_ids: torch.Tensor):
     return n, _dev(slot_ids, "slot_ids", torch.int32, (n,), pool.device)
 
 
+def _done(status: int) -> bool:
+    """Whether the native path made the call (raising its error); -1: it did not."""
+    if status > 0:
+        _check(status)
+    return status == 0
+
+
 def stepq_pool_load(pool: Pool, slot_ids, state, r, c, stream=None):
+    if _done(_native.scaled(0, pool._plain, slot_ids, state, r, c, stream)):
+        return
     n, ids = _ids(pool, slot_ids)
     P = pool
     _check(lib().stepq_pool_load(
@@ -333,14 +354,20 @@ def _step_args(pool: Pool, slot_ids, q, k, v, gate, beta, o, stream, kda: bool):
 
 
 def stepq_decode_step(pool: Pool, slot_ids, q, k, v, alpha, beta, o, stream=None):
+    if _done(_native.decode(pool._plain, slot_ids, q, k, v, alpha, beta, o, stream, 0)):
+        return
     _check(lib().stepq_decode_step(*_step_args(pool, slot_ids, q, k, v, alpha, beta, o, stream, False)))
 
 
 def stepq_decode_step_kda(pool: Pool, slot_ids, q, k, v, gate, beta, o, stream=None):
+    if _done(_native.decode(pool._plain, slot_ids, q, k, v, gate, beta, o, stream, STEPQ_STEP_KDA_GATE)):
+        return
     _check(lib().stepq_decode_step_kda(*_step_args(pool, slot_ids, q, k, v, gate, beta, o, stream, True)))
 
 
 def stepq_decode_step_ex(pool: Pool, slot_ids, q, k, v, gate, beta, o, flags: int, stream=None):
+    if _done(_native.decode(pool._plain, slot_ids, q, k, v, gate, beta, o, stream, flags)):
+        return
     a = _step_args(pool, slot_ids, q, k, v, gate, beta, o, stream, bool(flags & STEPQ_STEP_KDA_GATE))
     _check(lib().stepq_decode_step_ex(*a[:9], ctypes.c_uint32(flags), *a[9:]))
 
@@ -356,6 +383,8 @@ def stepq_pool_set_row_weight(pool: Pool, w, stream=None):
 
 
 def stepq_pool_dequant(pool: Pool, slot_ids, out, stream=None):
+    if _done(_native.tiles(0, pool._plain, slot_ids, out, stream)):
+        return
     n, ids = _ids(pool, slot_ids)
     P = pool
     _check(lib().stepq_pool_dequant(pool.handle, ids, n,
@@ -364,6 +393,8 @@ def stepq_pool_dequant(pool: Pool, slot_ids, out, stream=None):
 
 
 def stepq_pool_export(pool: Pool, slot_ids, codes, r, c, stream=None):
+    if _done(_native.scaled(2, pool._plain, slot_ids, codes, r, c, stream)):
+        return
     n, ids = _ids(pool, slot_ids)
     P = pool
     _check(lib().stepq_pool_export(
@@ -374,6 +405,8 @@ def stepq_pool_export(pool: Pool, slot_ids, codes, r, c, stream=None):
 
 
 def stepq_pool_import(pool: Pool, slot_ids, codes, r, c, stream=None):
+    if _done(_native.scaled(1, pool._plain, slot_ids, codes, r, c, stream)):
+        return
     n, ids = _ids(pool, slot_ids)
     P = pool
     _check(lib().stepq_pool_import(
@@ -386,6 +419,8 @@ def stepq_pool_import(pool: Pool, slot_ids, codes, r, c, stream=None):
 def stepq_pool_export_pivots(pool: Pool, slot_ids, pivots, stream=None):
     """pivots: [n][Hv][d_k][d_v] torch.int16 or uint16 on the pool's device
     (binary16 bit patterns of the pivot rows, zeros elsewhere)."""
+    if _done(_native.tiles(1, pool._plain, slot_ids, pivots, stream)):
+        return
     n, ids = _ids(pool, slot_ids)
     P = pool
     _check(lib().stepq_pool_export_pivots(pool.handle, ids, n,
@@ -393,6 +428,8 @@ def stepq_pool_export_pivots(pool: Pool, slot_ids, pivots, stream=None):
 
 
 def stepq_pool_import_pivots(pool: Pool, slot_ids, pivots, stream=None):
+    if _done(_native.tiles(2, pool._plain, slot_ids, pivots, stream)):
+        return
     n, ids = _ids(pool, slot_ids)
     P = pool
     _check(lib().stepq_pool_import_pivots(pool.handle, ids, n,

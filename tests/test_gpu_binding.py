@@ -1,0 +1,86 @@
+"""The binding's native argument checks: arguments that are not plainly what a
+call takes reach the Python checks (which raise, or take them), streams are
+honoured in every form, and a closed pool is refused."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_38169_amd import stepq
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0)
+B, H, DK, DV = 2, 2, 16, 64
+
+
+def _pool():
+    pool = stepq.Pool(3, H, H, DK, DV, np.full((H, DK), 8, np.uint8), device=DEV)
+    ids = torch.arange(3, dtype=torch.int32, device=DEV)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    S = torch.randn((3, H, DK, DV), generator=g, device=DEV)
+    r, c = stepq.stepq_setup_fit(S.cpu())
+    pool.load(ids, S, torch.from_numpy(r).to(DEV), torch.from_numpy(c).to(DEV))
+    return pool
+
+
+def _args():
+    g = torch.Generator(device=DEV).manual_seed(2)
+    rnd = lambda *s: torch.rand(s, generator=g, device=DEV)
+    return dict(slot_ids=torch.tensor([2, 0], dtype=torch.int32, device=DEV), q=rnd(B, H, DK), k=rnd(B, H, DK),
+                v=rnd(B, H, DV), alpha=rnd(B, H), beta=rnd(B, H), o=torch.zeros((B, H, DV), device=DEV))
+
+
+BAD = {
+    "cpu q": (ValueError, lambda a: a.update(q=a["q"].cpu())),
+    "half q": (TypeError, lambda a: a.update(q=a["q"].half())),
+    "bf16 k": (TypeError, lambda a: a.update(k=a["k"].bfloat16())),
+    "short v": (ValueError, lambda a: a.update(v=a["v"][..., :32].contiguous())),
+    "strided k": (ValueError, lambda a: a.update(k=a["k"].repeat(1, 1, 2)[..., ::2])),
+    "kda gate": (ValueError, lambda a: a.update(alpha=a["alpha"][..., None].expand(B, H, DK).contiguous())),
+    "int64 ids": (TypeError, lambda a: a.update(slot_ids=a["slot_ids"].long())),
+    "2-d ids": (ValueError, lambda a: a.update(slot_ids=a["slot_ids"][None])),
+    "numpy beta": (TypeError, lambda a: a.update(beta=a["beta"].cpu().numpy())),
+    "too many slots": (stepq.StepqError, lambda a: a.update({k: torch.cat([v, v]) for k, v in a.items()})),
+}
+
+
+@pytest.mark.parametrize("what", list(BAD))
+def test_bad_arguments_raise(what):
+    pool, a = _pool(), _args()
+    before = pool.memory.clone()
+    err, spoil = BAD[what]
+    spoil(a)
+    with pytest.raises(err):
+        pool.step(**a)
+    assert torch.equal(before, pool.memory)
+
+
+def test_plain_and_other_forms_agree():
+    """Default, integer and object streams, and tensor subclasses (which the
+    native checks leave to the Python ones), give one result."""
+    side = torch.cuda.Stream()
+    forms = [None, side, side.cuda_stream, "parameter", "with"]
+    images = []
+    for f in forms:
+        pool, a = _pool(), _args()
+        torch.cuda.synchronize()
+        if f == "parameter":
+            a["q"] = torch.nn.Parameter(a["q"])
+            pool.step(**a)
+        elif f == "with":
+            with torch.cuda.stream(side):
+                pool.step(**a)
+        else:
+            pool.step(**a, stream=f)
+        torch.cuda.synchronize()
+        images.append((pool.memory.clone(), a["o"].clone()))
+    for m, o in images[1:]:
+        assert torch.equal(m, images[0][0]) and torch.equal(o, images[0][1])
+
+
+def test_closed_pool_is_refused():
+    pool, a = _pool(), _args()
+    pool.close()
+    with pytest.raises(stepq.StepqError):
+        pool.step(**a)
+    with pytest.raises(stepq.StepqError):
+        pool.dequant(a["slot_ids"], torch.empty((B, H, DK, DV), device=DEV))
