@@ -242,9 +242,10 @@ __device__ __forceinline__ void tile_of(const DecodeArgs &a, uint32_t tile_bytes
     t.b = fdiv(l, a.div_heads);
     int j = l - t.b * a.n_heads;
     if (a.head_list) {
-        // rotate each request's heads by its index: tiles of one head then do
-        // not recur at the same launch position modulo the CUs of an XCD
-        j += t.b - a.n_heads * fdiv(j + t.b, a.div_heads);
+        // rotate each request's heads by b a.head_rot: the tiles that one CU
+        // gets (those 32 apart in an XCD's run) are then not all of one kind
+        j += t.b * a.head_rot;
+        j -= a.n_heads * fdiv(j, a.div_heads);
         const LaunchHead lh = a.head_list[j];
         t.h = lh.h;
         t.off = lh.tile_off;

@@ -42,6 +42,7 @@ struct DecodeArgs {
     const LaunchHead *head_list;
     int32_t n_heads;
     FastDiv div_heads;       // divide by n_heads
+    int32_t head_rot;        // heads of head_list that each request's order is rotated by (below n_heads)
     int32_t pairs;           // row pairs of the launch's largest head (the slot bodies)
     // Whole FP16 heads in a row-absmax step: their column factors become 1
     // (the baseline's c' = 1); their values update as in every other mode.
