@@ -22,6 +22,20 @@ __device__ __forceinline__ float act_ld(const void *p, size_t i)
     }
 }
 
+// The same in two halves: the load, and the value where it is first needed.
+template <bool BF16>
+__device__ __forceinline__ uint32_t act_bits(const void *p, size_t i)
+{
+    if constexpr (BF16) return static_cast<const uint16_t *>(p)[i];
+    else return static_cast<const uint32_t *>(p)[i];
+}
+
+template <bool BF16>
+__device__ __forceinline__ float act_value(uint32_t bits)
+{
+    return __uint_as_float(BF16 ? bits << 16 : bits);
+}
+
 // The code words of one tile, addressed through a buffer resource: the tile
 // base is uniform (scalar registers) and each thread adds a 32-bit offset, so
 // no 64-bit per-lane addresses are formed or kept live.  Word accesses stream
@@ -231,6 +245,22 @@ struct TileCtx {
     float alpha, beta;
 };
 
+// A head's layout record, read through the scalar cache (the table does not
+// change during a launch, which the compiler cannot see).
+__device__ __forceinline__ HeadInfo head_info(const PoolView &P, int h)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *ConstWords;
+    static_assert(sizeof(HeadInfo) % 4 == 0, "whole words");
+    const ConstWords p = (ConstWords)(reinterpret_cast<uintptr_t>(P.heads + h));
+    union {
+        uint32_t w[sizeof(HeadInfo) / 4];
+        HeadInfo hi;
+    } u;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(HeadInfo) / 4; ++i) u.w[i] = p[i];
+    return u.hi;
+}
+
 // The (request, value head) tile of this workgroup among the batch x
 // n_heads tiles of the launch, in launch order or in XCD runs
 // (a.launch_order); t.tile = b Hv + h indexes the activations.
@@ -261,35 +291,80 @@ __device__ __forceinline__ void tile_of(const DecodeArgs &a, uint32_t tile_bytes
     t.hq = fdiv(t.h, a.pool.div_g);
 }
 
-// Per-tile operands of thread tid, loaded together at the start of a tile:
-// k_i, q_i for logical row i = tid; r_p and the logical index of physical
-// row p = tid; c_j, v_j for column j = tid.
+// Per-tile operands, loaded together at the start of a tile.  Rows belong to
+// threads 0 .. 127 (waves 0 and 1): k_i, q_i for logical row i = tid, r_p and
+// the logical index of physical row p = tid.  Columns belong to threads 128 on
+// (waves 2 and 3): c_j, v_j for column j = tid - 128.  Wave i of every workgroup
+// sits on SIMD i, so the row and the column phases share the SIMDs evenly, and
+// no wave waits for one group of loads before it issues the other (with both
+// on waves 0 and 1, c and v were requested only after the code words had
+// arrived: 48 launches of 4 requests x 32 heads 236 -> 229 us, 128 requests x 32
+// heads of mixed rows with channel-wise gates 28.3 -> 27.3 us).
+template <bool BF16>
 struct RowColOps {
-    float k, q, r, c, v;
-    float d;                    // channel-wise gate of logical row tid (diagonal gate only)
+    uint32_t kb, qb, db, vb;    // activations as loaded: a conversion beside the load would wait for it
+    float r, c;
     int perm;
+
+    __device__ __forceinline__ float k() const { return act_value<BF16>(kb); }
+    __device__ __forceinline__ float q() const { return act_value<BF16>(qb); }
+    __device__ __forceinline__ float d() const { return act_value<BF16>(db); }  // gate of logical row tid (diagonal only)
+    __device__ __forceinline__ float v() const { return act_value<BF16>(vb); }
 };
 
+// The column a thread owns in the column phases, or -1.
+template <int DV>
+__device__ __forceinline__ int own_column()
+{
+    // whole waves: the wave's first thread decides, a scalar test
+    const int first = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) - 128;
+    return first >= 0 && first < DV ? static_cast<int>(threadIdx.x) - 128 : -1;
+}
+
+// dk: the rows of the tile (128 in the compiled bodies).  The choice between
+// rows and columns is a scalar branch: as a lane mask, the one group's loads
+// would wait for the other's registers.
 template <bool BF16, bool DIAG, int DV>
-__device__ __forceinline__ RowColOps load_ops(const DecodeArgs &a, int tile, int b, int hq, int h, const float *rr,
-                                              const float *cc)
+__device__ __forceinline__ RowColOps<BF16> load_ops(const DecodeArgs &a, int dk, int tile, int b, int hq, int h,
+                                              const float *rr, const float *cc)
 {
     const PoolView &P = a.pool;
-    const int tid = threadIdx.x;
-    RowColOps op{0.f, 0.f, 0.f, 0.f, 0.f, 1.f, 0};
-    if (tid < P.dk) {
-        if constexpr (DIAG) op.d = act_ld<BF16>(a.alpha, static_cast<size_t>(tile) * P.dk + tid);
-        const size_t off = (static_cast<size_t>(b) * P.Hqk + hq) * P.dk + tid;
-        op.k = act_ld<BF16>(a.k, off);
-        op.q = act_ld<BF16>(a.q, off);
-        op.r = rr[tid];
-        op.perm = P.perm[h * P.dk + tid];
-    }
-    if (tid < DV) {
-        op.c = cc[tid];
-        op.v = act_ld<BF16>(a.v, static_cast<size_t>(tile) * DV + tid);
+    const unsigned tid = threadIdx.x;
+    const int first = __builtin_amdgcn_readfirstlane(static_cast<int>(tid));     // the wave's first thread
+    constexpr size_t E = BF16 ? 2 : 4;
+    RowColOps<BF16> op;
+    if (first < 128) {
+        if (dk == 128 || tid < static_cast<unsigned>(dk)) {
+            const size_t off = (static_cast<size_t>(b) * P.Hqk + hq) * dk * E;
+            op.kb = act_bits<BF16>(static_cast<const char *>(a.k) + off, tid);
+            op.qb = act_bits<BF16>(static_cast<const char *>(a.q) + off, tid);
+            if constexpr (DIAG)
+                op.db = act_bits<BF16>(static_cast<const char *>(a.alpha) + static_cast<size_t>(tile) * dk * E, tid);
+            op.r = rr[tid];
+            op.perm = (P.perm + static_cast<size_t>(h) * dk)[tid];
+        }
+    } else if (first - 128 < DV) {
+        const unsigned j = tid - 128u;
+        op.c = cc[j];
+        op.vb = act_bits<BF16>(static_cast<const char *>(a.v) + static_cast<size_t>(tile) * DV * E, j);
     }
     return op;
+}
+
+// The level table in scalar registers from the start of the tile: an indexed
+// read where the row constants are formed would be a vector load from the
+// argument block in the middle of the tile's dependent chain.
+__device__ __forceinline__ LevelTable hold_levels(const LevelTable &t)
+{
+    LevelTable r = t;
+    asm volatile("" : "+s"(r.iq[0]), "+s"(r.iq[1]), "+s"(r.iq[2]), "+s"(r.fq[0]), "+s"(r.fq[1]), "+s"(r.fq[2]));
+    return r;
+}
+
+// Entry of a width's table for rows of bw bits, by selects.
+__device__ __forceinline__ float by_width(const float (&t)[3], int bw)
+{
+    return bw == 8 ? t[0] : (bw == 4 ? t[1] : t[2]);
 }
 
 // Row constants into LDS, indexed by row-table slot, and q.k.  Two barriers;
@@ -297,19 +372,19 @@ __device__ __forceinline__ RowColOps load_ops(const DecodeArgs &a, int tile, int
 // from the LDS copy of k and q.
 // SCALED: av and al come divided by the row width's clamp_scale, the form
 // the frozen-scale requantization works in (requant_word).
-template <bool DIAG, int DV, bool SCALED = false>
+template <bool DIAG, int DV, bool SCALED = false, class Ops>
 __device__ __forceinline__ float row_constants(const HeadInfo &hi, int dk, float alpha, float beta,
-                                               const RowColOps &op, DecodeShared<DV> &sh, const LevelTable &lv)
+                                               const Ops &op, DecodeShared<DV> &sh, const LevelTable &lv)
 {
     const int tid = threadIdx.x;
     if (tid < dk) {
-        sh.sk[tid] = op.k;
-        sh.sq[tid] = op.q;
+        sh.sk[tid] = op.k();
+        sh.sq[tid] = op.q();
         sh.sr[tid] = op.r;
         sh.sperm[tid] = op.perm;
-        if constexpr (DIAG) sh.sd[tid] = op.d;
+        if constexpr (DIAG) sh.sd[tid] = op.d();
     }
-    if (tid < DV) sh.cpiv[tid] = op.c;
+    if (own_column<DV>() >= 0) sh.cpiv[tid - 128] = op.c;
     __syncthreads();
     float kq = 0.f;
     if (tid < hi.n16) {
@@ -334,9 +409,8 @@ __device__ __forceinline__ float row_constants(const HeadInfo &hi, int dk, float
             const float qi = sh.sq[i];
             const float rp = sh.sr[p];
             // level of an unpacked field 2^(8-b) q: times fq (N1: 1/127, 1/112, 1/64)
-            const int wi = bw == 8 ? 0 : (bw == 4 ? 1 : 2);
-            const float qb = lv.iq[wi];
-            const float fq = lv.fq[wi];
+            const float qb = by_width(lv.iq, bw);
+            const float fq = by_width(lv.fq, bw);
             const float di = DIAG ? sh.sd[i] : 1.0f;       // the gate folds into both row weights
             const float rs = rp * fq * di;
             kt = ki * rs;
@@ -513,24 +587,24 @@ __device__ __forceinline__ int weight_scale_exp(float m)
 // Two barriers; the operand table is complete only after one more.
 // SCALED: av and al come divided by the row width's clamp_scale, the form
 // the frozen-scale requantization works in (requant_field_p).
-template <bool DIAG, int M8, int M4, int M2, int DV, bool SCALED = false>
-__device__ __forceinline__ float row_constants_mfma(float beta, const RowColOps &op, DecodeShared<DV> &sh,
+template <bool DIAG, int M8, int M4, int M2, int DV, bool SCALED = false, class Ops>
+__device__ __forceinline__ float row_constants_mfma(float beta, const Ops &op, DecodeShared<DV> &sh,
                                                     const LevelTable &lv, int &ek, int &eq)
 {
     constexpr int X4 = 8 * M8, X2 = 8 * M8 + 16 * M4;
     const int tid = threadIdx.x;
     if (tid < 128) {
-        sh.sk[tid] = op.k;
-        sh.sq[tid] = op.q;
-        if constexpr (DIAG) sh.sd[tid] = op.d;
+        sh.sk[tid] = op.k();
+        sh.sq[tid] = op.q();
+        if constexpr (DIAG) sh.sd[tid] = op.d();
     }
     __syncthreads();
     float kq = 0.f, kt = 0.f, qt = 0.f;
     if (tid < 128) {
         const int p = tid;
-        const int wi = p < X4 ? 0 : (p < X2 ? 1 : 2);
-        const float qb = lv.iq[wi];
-        const float fq = lv.fq[wi];
+        const int bw = p < X4 ? 8 : (p < X2 ? 4 : 2);
+        const float qb = by_width(lv.iq, bw);
+        const float fq = by_width(lv.fq, bw);
         const float ki = sh.sk[op.perm];
         const float qi = sh.sq[op.perm];
         const float di = DIAG ? sh.sd[op.perm] : 1.0f;
@@ -589,19 +663,20 @@ __device__ __forceinline__ float row_constants_mfma(float beta, const RowColOps 
 // slot_row (empty slots get zero weights and update factors, so their zero
 // codes stay zero).  Also the pivot rows' constants (pvc) and c (cpiv), as
 // in row_constants.  Two barriers; the operand table needs one more.
-template <bool DIAG, int M8, int M4, int M2, int DV, bool SCALED = false>
+template <bool DIAG, int M8, int M4, int M2, int DV, bool SCALED = false, class Ops>
 __device__ __forceinline__ float row_constants_mfma_piv(const HeadInfo &hi, float alpha, float beta,
-                                                        const RowColOps &op, DecodeShared<DV> &sh,
+                                                        const Ops &op, DecodeShared<DV> &sh,
                                                         const LevelTable &lv, int &ek, int &eq)
 {
     const int tid = threadIdx.x;
     if (tid < 128) {
-        sh.sk[tid] = op.k;
-        sh.sq[tid] = op.q;
+        sh.sk[tid] = op.k();
+        sh.sq[tid] = op.q();
         sh.sr[tid] = op.r;
         sh.sperm[tid] = op.perm;
-        sh.cpiv[tid] = op.c;
-        if constexpr (DIAG) sh.sd[tid] = op.d;
+        if constexpr (DIAG) sh.sd[tid] = op.d();
+    } else if (own_column<DV>() >= 0) {
+        sh.cpiv[tid - 128] = op.c;
     }
     __syncthreads();
     float kq = 0.f, kt = 0.f, qt = 0.f;
@@ -620,16 +695,15 @@ __device__ __forceinline__ float row_constants_mfma_piv(const HeadInfo &hi, floa
         const int p = slot_row(hi, x, bw);
         float av = 0.f, al = 0.f;
         if (p >= 0) {
-            const int wi = bw == 8 ? 0 : (bw == 4 ? 1 : 2);
             const int i = sh.sperm[p];
             const float r = sh.sr[p];
             const float ki = sh.sk[i], qi = sh.sq[i];
             const float di = DIAG ? sh.sd[i] : 1.0f;
-            const float rs = r * lv.fq[wi] * di;
+            const float rs = r * by_width(lv.fq, bw) * di;
             kt = ki * rs;
             qt = qi * rs;
             const float sc = SCALED ? (bw == 8 ? 1.0f / 256.0f : (bw == 4 ? (1.0f / 14.0f) : 0.5f)) : 1.0f;
-            av = beta * ki * (lv.iq[wi] * sc) * __builtin_amdgcn_rcpf(r);
+            av = beta * ki * (by_width(lv.iq, bw) * sc) * __builtin_amdgcn_rcpf(r);
             al = di * (bw == 8 ? sc : (bw == 4 ? (1.0f / 16.0f) * sc : (1.0f / 64.0f) * sc));
             kq += qi * ki;
         }
@@ -679,8 +753,8 @@ __device__ __forceinline__ float row_constants_mfma_piv(const HeadInfo &hi, floa
 }
 
 // Column sums of the per-thread partials, residual, readout, column factor
-// of the code-space update.  cj, vj: column tid's scale and value (threads
-// < DV, loaded at the start of the tile).  Ends with a barrier.
+// of the code-space update.  cj, vj: the scale and value of the column the
+// thread owns (own_column).  Ends with a barrier.
 template <int DV, class SH>
 __device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta, SH &sh,
                                             float kappa, float cj, float vj);
@@ -703,10 +777,8 @@ __device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float
                                             float kappa, float cj, float vj)
 {
     constexpr int NSL = 256 / (DV / 4);
-    const int tid = threadIdx.x;
     __syncthreads();
-    if (tid < DV) {
-        const int j = tid;
+    if (const int j = own_column<DV>(); j >= 0) {
         const float *rk = reinterpret_cast<const float *>(&sh.red[0][0][0]);
         const float *rq = reinterpret_cast<const float *>(&sh.red[1][0][0]);
         float sk = rk[j], sq = rq[j];
@@ -1032,17 +1104,18 @@ __device__ __forceinline__ void rowmix_columns4(const DecodeShared<128> &sh, con
 // thread's 16 code words (0 past the head's last group); pr: its pivot row.
 // ALLCOLS: the four columns in one pass (rowmix_columns4), else one at a
 // time (fewer registers).
-template <bool DIAG, bool SCALED, bool ALLCOLS = false, class W, class F>
+template <bool DIAG, bool SCALED, bool ALLCOLS = false, class W, class F, class Ops>
 __device__ __forceinline__ void rowmix_sums(const DecodeArgs &a, const TileCtx &t, DecodeShared<128> &sh,
                                             const W &w, const PivotRegs<128, kCompactPivots> &pr,
-                                            const RowColOps &op, int g8, int ng, F &&constants_done)
+                                            const Ops &op, const LevelTable &lv, int g8, int ng,
+                                            F &&constants_done)
 {
     const int tid = threadIdx.x;
     const int cg = tid & 31, slice = tid >> 5;
     // v_j waits in LDS for the column phase (c_j is kept there for the pivot
     // rows), so neither is held in registers through the row sums
-    if (tid < 128) sh.bcol[tid] = op.v;
-    const float kappa = uniform_f(row_constants<DIAG, 128, SCALED>(t.hi, 128, t.alpha, t.beta, op, sh, a.pool.lv));
+    if (own_column<128>() >= 0) sh.bcol[tid - 128] = op.v();
+    const float kappa = uniform_f(row_constants<DIAG, 128, SCALED>(t.hi, 128, t.alpha, t.beta, op, sh, lv));
     constants_done();
     int ek, eq;
     row_operands_rowmix(t.hi, sh, ek, eq);
@@ -1283,12 +1356,22 @@ __device__ __forceinline__ void decode_f16head(const DecodeArgs &a, const TileCt
     float vj = 0.f;
     int perm = 0;
     if (tid < 128) {
-        const size_t off = (static_cast<size_t>(t.b) * P.Hqk + t.hq) * 128 + tid;
-        sh.sk[tid] = act_ld<BF16>(a.k, off);
-        sh.sq[tid] = act_ld<BF16>(a.q, off);
-        if constexpr (DIAG) sh.sd[tid] = act_ld<BF16>(a.alpha, static_cast<size_t>(t.tile) * 128 + tid);
-        perm = P.perm[t.h * 128 + tid];
-        vj = act_ld<BF16>(a.v, static_cast<size_t>(t.tile) * 128 + tid);
+        constexpr size_t E = BF16 ? 2 : 4;
+        const size_t off = (static_cast<size_t>(t.b) * P.Hqk + t.hq) * 128 * E;
+        const unsigned row = tid;
+        perm = (P.perm + static_cast<size_t>(t.h) * 128)[row];
+        const float ki = act_ld<BF16>(static_cast<const char *>(a.k) + off, row);
+        const float qi = act_ld<BF16>(static_cast<const char *>(a.q) + off, row);
+        float di = 1.0f;
+        if constexpr (DIAG)
+            di = act_ld<BF16>(static_cast<const char *>(a.alpha) + static_cast<size_t>(t.tile) * 128 * E, row);
+        sh.sk[tid] = ki;
+        sh.sq[tid] = qi;
+        if constexpr (DIAG) sh.sd[tid] = di;
+    } else {
+        constexpr size_t E = BF16 ? 2 : 4;
+        const unsigned col = tid - 128;
+        vj = act_ld<BF16>(static_cast<const char *>(a.v) + static_cast<size_t>(t.tile) * 128 * E, col);
     }
     __syncthreads();
     float kq = 0.f;
@@ -1321,7 +1404,7 @@ __device__ __forceinline__ void decode_f16head(const DecodeArgs &a, const TileCt
         acQ[3] = fma_mix<1>(c.y, S[m].y, acQ[3]);
     }
     column_phase<128>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, acK, acQ, 1.0f, vj);
-    if (a.f16_c_one && tid < 128) const_cast<float *>(t.cc)[tid] = 1.0f;
+    if (a.f16_c_one && tid >= 128) const_cast<float *>(t.cc)[tid - 128] = 1.0f;
 
     const float4 b4 = *reinterpret_cast<const float4 *>(&sh.bcol[4 * cg]);   // delta_j
     const float dl[4] = {b4.x, b4.y, b4.z, b4.w};

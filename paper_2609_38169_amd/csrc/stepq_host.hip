@@ -355,6 +355,7 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
     const bool bf16 = act_dtype == STEPQ_BF16;
     a.f16_c_one = 0;
     a.launch_order = (flags & STEPQ_STEP_ADJACENT_SLOTS) ? 1 : 0;
+    int pairs = p->plan.pairs;
     auto launch = [&](int layout) {
         a.head_rot = head_rotation(a.batch, a.n_heads);
         if (layout == stepq::kF16HeadLayout) {
@@ -364,13 +365,12 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
             a.f16_c_one = 0;
             return r;
         }
-        return (flags & STEPQ_STEP_REFIT)        ? stepq::launch_decode_refit(a, bf16, diag, layout, s)
-               : (flags & STEPQ_STEP_ROW_ABSMAX) ? stepq::launch_decode_rowmax(a, bf16, diag, layout, s)
+        return (flags & STEPQ_STEP_REFIT)        ? stepq::launch_decode_refit(a, bf16, diag, layout, pairs, s)
+               : (flags & STEPQ_STEP_ROW_ABSMAX) ? stepq::launch_decode_rowmax(a, bf16, diag, layout, pairs, s)
                                                  : stepq::launch_decode(a, bf16, diag, layout, s);
     };
     hipError_t e = hipSuccess;
     const stepq::LaunchPlan &plan = p->plan;
-    a.pairs = plan.pairs;
     // the combined launches the refit has bodies for: several uniform layouts
     // and whole FP16 heads, or one uniform layout and its padded pivot heads
     const bool refit_multi = (flags & STEPQ_STEP_REFIT) && stepq::refit_combined(plan.mixed_code);
@@ -392,7 +392,7 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
         for (size_t c = 0; c < plan.cls_code.size() && e == hipSuccess; ++c) {
             a.head_list = p->d_head_order + plan.cls_off[c];
             a.n_heads = plan.cls_cnt[c];
-            a.pairs = plan.cls_pairs[c];
+            pairs = plan.cls_pairs[c];
             a.div_heads = p->div_cls[c];
             e = launch(plan.cls_code[c]);
         }

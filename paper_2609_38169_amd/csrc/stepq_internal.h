@@ -36,14 +36,13 @@ struct DecodeArgs {
     const void *q, *k, *v, *alpha, *beta;
     float *o;
     int32_t batch;
+    int32_t head_rot;        // heads of head_list that each request's order is rotated by (below n_heads)
     // The value heads one launch covers: head_list[0 .. n_heads) (device),
     // or every head 0 .. Hv-1 in order when head_list is NULL (then every
     // head has the same tile size).  The grid is batch x n_heads workgroups.
     const LaunchHead *head_list;
     int32_t n_heads;
     FastDiv div_heads;       // divide by n_heads
-    int32_t head_rot;        // heads of head_list that each request's order is rotated by (below n_heads)
-    int32_t pairs;           // row pairs of the launch's largest head (the slot bodies)
     // Whole FP16 heads in a row-absmax step: their column factors become 1
     // (the baseline's c' = 1); their values update as in every other mode.
     int32_t f16_c_one;
@@ -84,10 +83,13 @@ hipError_t launch_decode(const DecodeArgs &a, bool bf16, bool diag, int pool_lay
 // The decode step followed by the online dual-axis refit of both scale
 // vectors (the codes are requantized against the refitted scales, which
 // replace the stored ones).
-hipError_t launch_decode_refit(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, hipStream_t stream);
+// pairs: the most row pairs of a head of the launch (slot_pairs).
+hipError_t launch_decode_refit(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, int pairs,
+                               hipStream_t stream);
 // The decode step with the single-axis baseline's requantization: row
 // factors r'_i = max_j |X_ij|, column factors 1.
-hipError_t launch_decode_rowmax(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, hipStream_t stream);
+hipError_t launch_decode_rowmax(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, int pairs,
+                                hipStream_t stream);
 // Memory-only reference of a decode launch: the same tiles, order and
 // memory traffic (codes rewritten unchanged, o zeroed), no arithmetic.
 hipError_t launch_stream_ref(const DecodeArgs &a, bool bf16, hipStream_t stream);

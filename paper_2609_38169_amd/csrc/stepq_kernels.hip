@@ -45,6 +45,7 @@ __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCt
     constexpr int X4 = 8 * M8, X2 = 8 * M8 + 16 * M4;    // row-table starts of the 4- and 2-bit slots
     const int tid = threadIdx.x;
     const int cg = tid & 31, slice = tid >> 5;
+    const LevelTable lv = hold_levels(a.pool.lv);
     const CodeWords cw(t.codes, 1024u * M);
     uint32_t w[M];
 #pragma unroll
@@ -52,13 +53,13 @@ __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCt
     PivotRegs<128, kCompactPivots> pr;
     if constexpr (PIV) pivot_load<128, kCompactPivots>(t, slice, cg, pr);
 
-    const RowColOps op = load_ops<BF16, DIAG, 128>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    const RowColOps<BF16> op = load_ops<BF16, DIAG, 128>(a, 128, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
     int ek, eq;
     float kappa;
     if constexpr (PIV)
-        kappa = row_constants_mfma_piv<DIAG, M8, M4, M2, 128, true>(t.hi, t.alpha, t.beta, op, sh, a.pool.lv, ek, eq);
+        kappa = row_constants_mfma_piv<DIAG, M8, M4, M2, 128, true>(t.hi, t.alpha, t.beta, op, sh, lv, ek, eq);
     else
-        kappa = row_constants_mfma<DIAG, M8, M4, M2, 128, true>(t.beta, op, sh, a.pool.lv, ek, eq);
+        kappa = row_constants_mfma<DIAG, M8, M4, M2, 128, true>(t.beta, op, sh, lv, ek, eq);
 
     uint32_t Ub[4][4][2];
     unpack_row_pairs<M8, M4, M2>(w, Ub);
@@ -66,7 +67,7 @@ __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCt
     matvec_partials(sh, slice, cg, Ub, ek, eq);
     if constexpr (PIV) pivot_partials_slice(t, slice, cg, pr, sh);
 
-    column_sums<128>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, op.c, op.v);
+    column_sums<128>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, op.c, op.v());
 
     const float4 b4 = *reinterpret_cast<const float4 *>(&sh.bcol[4 * cg]);
     const float bc[4] = {b4.x, b4.y, b4.z, b4.w};
@@ -98,14 +99,15 @@ __device__ __forceinline__ void decode_generic(const DecodeArgs &a, const TileCt
     const int ngroups = static_cast<int>(t.hi.groups);
     // words of groups past the head's last lie in the zeroed tail of the
     // codes region or past it (read as 0): one uniform check per word-step
+    const LevelTable lv = hold_levels(a.pool.lv);
     const CodeWords cw(t.codes, t.hi.piv_off);
     uint32_t w[MMAX];
 #pragma unroll
     for (int m = 0; m < MMAX; ++m) w[m] = NSL * m < ngroups ? cw.load(tid + 256 * m) : 0u;
     PivotRegs<DV, PMAX> pr;
     pivot_load(t, slice, cg, pr);
-    const RowColOps op = load_ops<BF16, DIAG, DV>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
-    const float kappa = row_constants<DIAG, DV, true>(t.hi, a.pool.dk, t.alpha, t.beta, op, sh, a.pool.lv);
+    const RowColOps<BF16> op = load_ops<BF16, DIAG, DV>(a, a.pool.dk, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    const float kappa = row_constants<DIAG, DV, true>(t.hi, a.pool.dk, t.alpha, t.beta, op, sh, lv);
 
     float acK[4] = {0.f, 0.f, 0.f, 0.f}, acQ[4] = {0.f, 0.f, 0.f, 0.f};
     float U[16];
@@ -120,7 +122,7 @@ __device__ __forceinline__ void decode_generic(const DecodeArgs &a, const TileCt
         }
     }
     pivot_acc(t, slice, cg, pr, sh, acK, acQ);
-    column_phase<DV>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, acK, acQ, op.c, op.v);
+    column_phase<DV>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, acK, acQ, op.c, op.v());
 
     const float4 b4 = *reinterpret_cast<const float4 *>(&sh.bcol[4 * cg]);
     const float bc[4] = {b4.x, b4.y, b4.z, b4.w};
@@ -164,14 +166,15 @@ __device__ __forceinline__ void decode_rowmix(const DecodeArgs &a, const TileCtx
     // the buffer covers the codes region only (piv_off = 128 ng): the words
     // of groups past the head's last read 0 and their stores are dropped, so
     // each word-step needs one uniform check and no per-lane one
+    const LevelTable lv = hold_levels(a.pool.lv);
     const CodeWords cw(t.codes, t.hi.piv_off);
     uint32_t w[16];
 #pragma unroll
     for (int m = 0; m < 16; ++m) w[m] = 8 * m < ng ? cw.load(tid + 256 * m) : 0u;
     PivotRegs<128, kCompactPivots> pr;
     pivot_load<128, kCompactPivots>(t, slice, cg, pr);
-    const RowColOps op = load_ops<BF16, DIAG, 128>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
-    rowmix_sums<DIAG, true, true>(a, t, sh, w, pr, op, g8, ng, [] {});
+    const RowColOps<BF16> op = load_ops<BF16, DIAG, 128>(a, 128, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    rowmix_sums<DIAG, true, true>(a, t, sh, w, pr, op, lv, g8, ng, [] {});
 
     const float4 b4 = *reinterpret_cast<const float4 *>(&sh.bcol[4 * cg]);
     const float bc[4] = {b4.x, b4.y, b4.z, b4.w};
@@ -232,7 +235,7 @@ template <bool BF16, bool DIAG>
 __device__ __forceinline__ void run_rowmix(const DecodeArgs &a, TileCtx &t, int slot, DecodeShared<128> &sh)
 {
     const PoolView &P = a.pool;
-    t.hi = P.heads[t.h];
+    t.hi = head_info(P, t.h);
     uint8_t *rec = P.base + static_cast<uint64_t>(slot) * P.slot_bytes + t.hi.tile_off;
     t.codes = reinterpret_cast<uint32_t *>(rec);
     t.rr = reinterpret_cast<const float *>(rec + t.hi.r_off);
@@ -244,7 +247,7 @@ template <bool BF16, bool DIAG, int DV, bool COMPACT>
 __device__ __forceinline__ void run_generic(const DecodeArgs &a, TileCtx &t, int slot, DecodeShared<DV> &sh)
 {
     const PoolView &P = a.pool;
-    t.hi = P.heads[t.h];
+    t.hi = head_info(P, t.h);
     uint8_t *rec = P.base + static_cast<uint64_t>(slot) * P.slot_bytes + t.hi.tile_off;
     t.codes = reinterpret_cast<uint32_t *>(rec);
     t.rr = reinterpret_cast<const float *>(rec + t.hi.r_off);
@@ -357,7 +360,7 @@ __global__ __launch_bounds__(256) void stream_ref_kernel(DecodeArgs a, uint32_t 
     const PoolView &P = a.pool;
     TileCtx t;
     tile_of(a, 0u, t);
-    const HeadInfo hi = P.heads[t.h];
+    const HeadInfo hi = head_info(P, t.h);
     const int slot = a.slot_ids[t.b];
     uint8_t *rec = P.base + static_cast<uint64_t>(slot) * P.slot_bytes + hi.tile_off;
     const int tid = threadIdx.x;

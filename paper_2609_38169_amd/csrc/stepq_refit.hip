@@ -4,9 +4,10 @@
 
 namespace stepq {
 
-hipError_t launch_decode_refit(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, hipStream_t stream)
+hipError_t launch_decode_refit(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, int pairs,
+                               hipStream_t stream)
 {
-    return launch_refit_mode<Refit::DualAxis>(a, bf16, diag, pool_layout, stream);
+    return launch_refit_mode<Refit::DualAxis>(a, bf16, diag, pool_layout, pairs, stream);
 }
 
 }  // namespace stepq

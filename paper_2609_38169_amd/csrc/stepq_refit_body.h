@@ -101,7 +101,7 @@ __device__ __forceinline__ float refit_row(const float4 *part, int bw, float r_p
                                            float &h, float &W)
 {
     const float iq = bw == 8 ? (1.0f / 127.0f) : (bw == 4 ? (1.0f / 7.0f) : 1.0f);     // 1 / q_b
-    const float nu = lv.nu[bw == 8 ? 0 : (bw == 4 ? 1 : 2)];
+    const float nu = by_width(lv.nu, bw);
     if constexpr (MODE == Refit::RowAbsmax) {
         float mx = 0.f;
 #pragma unroll
@@ -333,6 +333,7 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
     const int cg = tid & 31, slice = tid >> 5;
     float *rr_out = const_cast<float *>(t.rr);
     float *cc_out = const_cast<float *>(t.cc);
+    const LevelTable lv = hold_levels(a.pool.lv);
     const CodeWords cw(t.codes, 1024u * M);
     uint32_t w[M];
 #pragma unroll
@@ -340,25 +341,23 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
     PivotRegs<128, kCompactPivots> pr;
     if constexpr (PIV) pivot_load<128, kCompactPivots>(t, slice, cg, pr);
 
-    const RowColOps op = load_ops<BF16, DIAG, 128>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
-    if (tid < 128) {
-        sh.ccol[tid] = op.c;
-        sh.wphys[tid] = a.pool.roww[t.h * 128 + tid];
-    }
+    const RowColOps<BF16> op = load_ops<BF16, DIAG, 128>(a, 128, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    if (tid < 128) sh.wphys[tid] = (a.pool.roww + static_cast<size_t>(t.h) * 128)[static_cast<unsigned>(tid)];
+    else sh.ccol[tid - 128] = op.c;
     // S^T k and S^T q on the matrix cores, as in the frozen-scale body
     int ek, eq;
     float kappa;
     if constexpr (PIV)
-        kappa = row_constants_mfma_piv<DIAG, M8, M4, M2, 128>(t.hi, t.alpha, t.beta, op, sh.d, a.pool.lv, ek, eq);
+        kappa = row_constants_mfma_piv<DIAG, M8, M4, M2, 128>(t.hi, t.alpha, t.beta, op, sh.d, lv, ek, eq);
     else
-        kappa = row_constants_mfma<DIAG, M8, M4, M2, 128>(t.beta, op, sh.d, a.pool.lv, ek, eq);
+        kappa = row_constants_mfma<DIAG, M8, M4, M2, 128>(t.beta, op, sh.d, lv, ek, eq);
     uint32_t Ub[4][4][2];
     unpack_row_pairs<M8, M4, M2>(w, Ub);
     __syncthreads();    // operand table written
     matvec_partials(sh.d, slice, cg, Ub, ek, eq);
     if constexpr (PIV) pivot_partials_slice(t, slice, cg, pr, sh.d);
 
-    column_sums<128>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh.d, kappa, op.c, op.v);
+    column_sums<128>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh.d, kappa, op.c, op.v());
 
     // pass 1: y on the old scales and the row partials
     float bc[4], cc[4];
@@ -394,14 +393,14 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
             const int p = slot_row(t.hi, tid, bw);
             if (p >= 0) {
                 rr_out[p] = refit_row<MODE, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]), bw, sh.d.sr[p],
-                                                sh.wphys[p], a.pool.lv, sh.hrow[tid], sh.wrow[tid]);
+                                                sh.wphys[p], lv, sh.hrow[tid], sh.wrow[tid]);
             } else {
                 sh.hrow[tid] = 0.f;
                 sh.wrow[tid] = 0.f;
             }
         } else {
             rr_out[tid] = refit_row<MODE, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]),
-                                              tid < X4 ? 8 : (tid < X2 ? 4 : 2), op.r, sh.wphys[tid], a.pool.lv,
+                                              tid < X4 ? 8 : (tid < X2 ? 4 : 2), op.r, sh.wphys[tid], lv,
                                               sh.hrow[tid], sh.wrow[tid]);
         }
     }
@@ -419,7 +418,7 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
         sh.u.cmax[slice][cg] = width_max(mx8, mx4, mx2);
     }
     __syncthreads();
-    if (tid < 128) refit_colmax<128>(sh, tid);
+    if (tid >= 128) refit_colmax<128>(sh, tid - 128);
     __syncthreads();
 
     // pass 3: fixed codes and the least-squares sums
@@ -437,7 +436,7 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
         sh.d.red[1][slice][cg] = make_float4(den[0], den[1], den[2], den[3]);
     }
     __syncthreads();
-    if (tid < 128) refit_colfit<128>(sh, tid, cc_out);
+    if (tid >= 128) refit_colfit<128>(sh, tid - 128, cc_out);
     __syncthreads();
 
     // pass 4: requantize on the new scales, store in place
@@ -463,7 +462,7 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
 // instructions.  Keeping the values and taking the width tests as scalar
 // branches, against bodies that unpacked the words again in each pass
 // (generic) or tested each lane's width in each word-step (row-mix): a
-// 512-request x 16-head row-unit map with channel-wise gates 120.7 -> 101.4 us
+// 512-request x 16-head row-unit map with channel-wise gates 120.7 -> 98.4 us
 // (1,942 -> 1,645 instructions per wave), 201 requests x 6 heads of random
 // 2/4/8-bit rows at d_k = 96, d_v = 64 16.0 -> 14.3 us.
 
@@ -543,6 +542,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     float *rr_out = const_cast<float *>(t.rr);
     float *cc_out = const_cast<float *>(t.cc);
     const SlotGeom g(t.hi, D::NSL == 8 ? 3 : 4);
+    const LevelTable lv = hold_levels(a.pool.lv);
     const SlotWords<DV> cw(t.codes, g, slice);
     uint32_t wa[NP], wb[NP];
     u32x16 w16;
@@ -557,11 +557,12 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     }
     PivotRegs<DV, PMAX> pr;
     pivot_load(t, slice, cg, pr);
-    const RowColOps op = load_ops<BF16, DIAG, DV>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    const RowColOps<BF16> op = load_ops<BF16, DIAG, DV>(a, dk, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
     const SlotRow row = slot_of_row<D::NSL>(t.hi, g, tid, dk);
     float w_row = 1.0f;
     if (MODE == Refit::DualAxis && row.slice >= 0) w_row = a.pool.roww[t.h * dk + tid];
-    if (tid < DV) sh.ccol[tid] = op.c;
+    const int col = own_column<DV>();
+    if (col >= 0) sh.ccol[col] = op.c;
     if (tid < D::NSL * D::NR) {
         (&sh.hrow[0][0])[tid] = 0.f;
         (&sh.wrow[0][0])[tid] = 0.f;
@@ -575,7 +576,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     // rounding boundary depends on their last bits.
     float Y[NP][8];
     if constexpr (ROWMIX) {
-        rowmix_sums<DIAG, false, true>(a, t, sh.d, w16, pr, op, g.g8, ng, [&] {
+        rowmix_sums<DIAG, false, true>(a, t, sh.d, w16, pr, op, lv, g.g8, ng, [&] {
             if (row.slice >= 0) {
                 // row-table slot of physical row tid: the integer rows in order
                 const int x = tid - static_cast<int>(t.hi.n16);
@@ -601,7 +602,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
         }
         slot_fields<NP, HAS2>(g, wa, wb, Y);
     } else {
-        const float kappa = slot_constants<DIAG>(t.hi, dk, t.alpha, t.beta, op, sh.d, a.pool.lv, row);
+        const float kappa = slot_constants<DIAG>(t.hi, dk, t.alpha, t.beta, op, sh.d, lv, row);
         slot_fields<NP, HAS2>(g, wa, wb, Y);
         float acK[4] = {0.f, 0.f, 0.f, 0.f}, acQ[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -650,12 +651,12 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     if (row.slice >= 0) {
         const float4 *part = reinterpret_cast<const float4 *>(&sh.u.rowp[row.slice][row.r * SH::PR]);
         float h, W;
-        rr_out[tid] = refit_row<MODE, SH::PR>(part, row.bw, op.r, w_row, a.pool.lv, h, W);
+        rr_out[tid] = refit_row<MODE, SH::PR>(part, row.bw, op.r, w_row, lv, h, W);
         sh.hrow[row.slice][row.r] = h;
         if constexpr (MODE == Refit::DualAxis) sh.wrow[row.slice][row.r] = W;
     }
     if constexpr (MODE == Refit::RowAbsmax) {
-        if (tid < DV) cc_out[tid] = 1.0f;
+        if (col >= 0) cc_out[col] = 1.0f;
     }
     __syncthreads();
 
@@ -701,7 +702,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
                                                fmaxf(top[2], mx[2] * f), fmaxf(top[3], mx[3] * f));
         }
         __syncthreads();
-        if (tid < DV) refit_colmax<DV>(sh, tid);
+        if (col >= 0) refit_colmax<DV>(sh, col);
         __syncthreads();
 
         // pass 3: fixed codes and the least-squares sums
@@ -719,7 +720,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
             sh.d.red[1][slice][cg] = make_float4(den[0], den[1], den[2], den[3]);
         }
         __syncthreads();
-        if (tid < DV) refit_colfit<DV>(sh, tid, cc_out);
+        if (col >= 0) refit_colfit<DV>(sh, col, cc_out);
         __syncthreads();
         ld4(&sh.gcol[4 * cg], gc);
     }
@@ -809,7 +810,7 @@ __global__ __launch_bounds__(256, refit_waves(NP)) void refit_kernel(DecodeArgs 
         default: run_f16head<BF16, DIAG>(a, t, slot, sh.d); break;
         }
     } else {
-        t.hi = P.heads[t.h];
+        t.hi = head_info(P, t.h);
         uint8_t *rec = P.base + static_cast<uint64_t>(slot) * P.slot_bytes + t.hi.tile_off;
         t.codes = reinterpret_cast<uint32_t *>(rec);
         t.rr = reinterpret_cast<const float *>(rec + t.hi.r_off);
@@ -821,9 +822,9 @@ __global__ __launch_bounds__(256, refit_waves(NP)) void refit_kernel(DecodeArgs 
 // Heads of any mix at the compiled pair count that holds the launch's
 // largest head.
 template <bool BF16, bool DIAG, Refit MODE>
-hipError_t launch_refit_slots(const DecodeArgs &a, unsigned grid, hipStream_t s)
+hipError_t launch_refit_slots(const DecodeArgs &a, int pairs, unsigned grid, hipStream_t s)
 {
-    const int np = slot_pairs_compiled(a.pairs, a.pool.dv);
+    const int np = slot_pairs_compiled(pairs, a.pool.dv);
     if (a.pool.dv == 64) {
         switch (np) {
         case 4: hipLaunchKernelGGL((refit_kernel<64, BF16, 0, DIAG, MODE, 4>), dim3(grid), dim3(256), 0, s, a); break;
@@ -846,7 +847,7 @@ hipError_t launch_refit_slots(const DecodeArgs &a, unsigned grid, hipStream_t s)
 }
 
 template <bool BF16, bool DIAG, Refit MODE>
-hipError_t launch_refit_any(const DecodeArgs &a, int layout, unsigned grid, hipStream_t s)
+hipError_t launch_refit_any(const DecodeArgs &a, int layout, int pairs, unsigned grid, hipStream_t s)
 {
     if (a.pool.dv == 128 && layout == kRowMix) {
         hipLaunchKernelGGL((refit_kernel<128, BF16, kRowMix, DIAG, MODE, kSlotPairs84>), dim3(grid), dim3(256), 0, s, a);
@@ -884,22 +885,22 @@ hipError_t launch_refit_any(const DecodeArgs &a, int layout, unsigned grid, hipS
         case kMixedPivotBase + 2:
             hipLaunchKernelGGL((refit_kernel<128, BF16, kMixedPivotBase + 2, DIAG, MODE>), dim3(grid), dim3(256), 0, s, a);
             break;
-        default: return launch_refit_slots<BF16, DIAG, MODE>(a, grid, s);
+        default: return launch_refit_slots<BF16, DIAG, MODE>(a, pairs, grid, s);
         }
         return hipGetLastError();
     }
-    return launch_refit_slots<BF16, DIAG, MODE>(a, grid, s);
+    return launch_refit_slots<BF16, DIAG, MODE>(a, pairs, grid, s);
 }
 
 template <Refit MODE>
-hipError_t launch_refit_mode(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, hipStream_t stream)
+hipError_t launch_refit_mode(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, int pairs, hipStream_t stream)
 {
     const unsigned grid = static_cast<unsigned>(a.batch) * static_cast<unsigned>(a.n_heads);
     if (grid == 0) return hipSuccess;
-    if (bf16) return diag ? launch_refit_any<true, true, MODE>(a, pool_layout, grid, stream)
-                          : launch_refit_any<true, false, MODE>(a, pool_layout, grid, stream);
-    return diag ? launch_refit_any<false, true, MODE>(a, pool_layout, grid, stream)
-                : launch_refit_any<false, false, MODE>(a, pool_layout, grid, stream);
+    if (bf16) return diag ? launch_refit_any<true, true, MODE>(a, pool_layout, pairs, grid, stream)
+                          : launch_refit_any<true, false, MODE>(a, pool_layout, pairs, grid, stream);
+    return diag ? launch_refit_any<false, true, MODE>(a, pool_layout, pairs, grid, stream)
+                : launch_refit_any<false, false, MODE>(a, pool_layout, pairs, grid, stream);
 }
 
 }  // namespace

@@ -36,10 +36,8 @@ struct RowmaxShared {
 __device__ __forceinline__ void column_sums_rowmax(const DecodeArgs &a, int tile, float alpha, float beta,
                                                    RowmaxShared &sh, float kappa, float cj, float vj)
 {
-    const int tid = threadIdx.x;
     __syncthreads();
-    if (tid < 128) {
-        const int j = tid;
+    if (const int j = own_column<128>(); j >= 0) {
         const float *rk = reinterpret_cast<const float *>(&sh.d.red[0][0][0]);
         const float *rq = reinterpret_cast<const float *>(&sh.d.red[1][0][0]);
         float sk = rk[j], sq = rq[j];
@@ -158,25 +156,26 @@ __device__ __forceinline__ void rowmax_uniform(const DecodeArgs &a, const TileCt
     constexpr int M = M8 + M4 + M2;
     const int tid = threadIdx.x;
     const int cg = tid & 31, slice = tid >> 5;
+    const LevelTable lv = hold_levels(a.pool.lv);
     const CodeWords cw(t.codes, 1024u * M);
     uint32_t w[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) w[m] = cw.load_m(tid, m);
-    const RowColOps op = load_ops<BF16, DIAG, 128>(a, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    const RowColOps<BF16> op = load_ops<BF16, DIAG, 128>(a, 128, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
     if (tid < 128) sh.d.sr[tid] = op.r;     // old row factor by physical row, for the new ones
     int ek, eq;
-    const float kappa = row_constants_mfma<DIAG, M8, M4, M2, 128>(t.beta, op, sh.d, a.pool.lv, ek, eq);
+    const float kappa = row_constants_mfma<DIAG, M8, M4, M2, 128>(t.beta, op, sh.d, lv, ek, eq);
     uint32_t Ub[4][4][2];
     unpack_row_pairs<M8, M4, M2>(w, Ub);
     __syncthreads();    // operand table written
     matvec_partials(sh.d, slice, cg, Ub, ek, eq);
-    column_sums_rowmax(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, op.c, op.v);
+    column_sums_rowmax(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, op.c, op.v());
 
     // The thread's 16 rows in two halves of 8: each half forms its z,
     // reduces its row maxima and is requantized before the next half's z
     // exist, so at most 32 z values are live
     float *part = reinterpret_cast<float *>(&sh.d.red[0][0][0]);    // [128 rows][16 lane pairs]
-    if (tid < 128) const_cast<float *>(t.cc)[tid] = 1.0f;    // c' = 1 (c was read at the start)
+    if (tid >= 128) const_cast<float *>(t.cc)[tid - 128] = 1.0f;    // c' = 1 (c was read at the start)
     rowmax_half<DIAG, M8, M4, M2, 0>(t, sh, Ub, part, cw);
     rowmax_half<DIAG, M8, M4, M2, 1>(t, sh, Ub, part, cw);
 }
@@ -214,7 +213,8 @@ hipError_t launch_rowmax_uniform(const DecodeArgs &a, int layout, unsigned grid,
 
 }  // namespace
 
-hipError_t launch_decode_rowmax(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, hipStream_t stream)
+hipError_t launch_decode_rowmax(const DecodeArgs &a, bool bf16, bool diag, int pool_layout, int pairs,
+                                hipStream_t stream)
 {
     if (a.pool.dv == 128 && pool_layout >= 1 && pool_layout <= kNumUniformLayouts) {
         const unsigned grid = static_cast<unsigned>(a.batch) * static_cast<unsigned>(a.n_heads);
@@ -224,7 +224,7 @@ hipError_t launch_decode_rowmax(const DecodeArgs &a, bool bf16, bool diag, int p
         return diag ? launch_rowmax_uniform<false, true>(a, pool_layout, grid, stream)
                     : launch_rowmax_uniform<false, false>(a, pool_layout, grid, stream);
     }
-    return launch_refit_mode<Refit::RowAbsmax>(a, bf16, diag, pool_layout, stream);
+    return launch_refit_mode<Refit::RowAbsmax>(a, bf16, diag, pool_layout, pairs, stream);
 }
 
 }  // namespace stepq

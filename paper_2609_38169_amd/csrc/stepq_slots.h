@@ -182,22 +182,22 @@ __device__ __forceinline__ SlotRow slot_of_row(const HeadInfo &hi, const SlotGeo
 }
 
 // Row constants by slot (slots without a row: 0).  Two barriers; returns q.k.
-template <bool DIAG, int DV, int NP>
+template <bool DIAG, int DV, int NP, class Ops>
 __device__ __forceinline__ float slot_constants(const HeadInfo &hi, int dk, float alpha, float beta,
-                                                const RowColOps &op, SlotShared<DV, NP> &sh, const LevelTable &lv,
+                                                const Ops &op, SlotShared<DV, NP> &sh, const LevelTable &lv,
                                                 const SlotRow &row)
 {
     using SH = SlotShared<DV, NP>;
     constexpr int NE = SH::NSL * SH::NR;
     const int tid = threadIdx.x;
     if (tid < dk) {
-        sh.sk[tid] = op.k;
-        sh.sq[tid] = op.q;
-        if constexpr (DIAG) sh.sd[tid] = op.d;
+        sh.sk[tid] = op.k();
+        sh.sq[tid] = op.q();
+        if constexpr (DIAG) sh.sd[tid] = op.d();
     }
-    if (tid < DV) {
-        sh.bcol[tid] = op.v;       // v_j and c_j wait in LDS for the column phase
-        sh.cpiv[tid] = op.c;
+    if (own_column<DV>() >= 0) {
+        sh.bcol[tid - 128] = op.v();       // v_j and c_j wait in LDS for the column phase
+        sh.cpiv[tid - 128] = op.c;
     }
     // slots without a row keep zero constants
     if (tid < NE) {
@@ -213,10 +213,9 @@ __device__ __forceinline__ float slot_constants(const HeadInfo &hi, int dk, floa
             const float di = DIAG ? sh.sd[op.perm] : 1.0f;
             kq = qi * ki;
             if (row.slice >= 0) {
-                const int wi = row.bw == 8 ? 0 : (row.bw == 4 ? 1 : 2);
-                const float rs = op.r * lv.fq[wi] * di;
+                const float rs = op.r * by_width(lv.fq, row.bw) * di;
                 sh.kq[row.slice][row.r] = make_float2(ki * rs, qi * rs);
-                sh.av[row.slice][row.r] = beta * ki * lv.iq[wi] * __builtin_amdgcn_rcpf(op.r);
+                sh.av[row.slice][row.r] = beta * ki * by_width(lv.iq, row.bw) * __builtin_amdgcn_rcpf(op.r);
                 sh.al[row.slice][row.r] = (DIAG ? di : alpha) *
                                           (row.bw == 8 ? 1.0f : (row.bw == 4 ? 1.0f / 16.0f : 1.0f / 64.0f));
             } else {
