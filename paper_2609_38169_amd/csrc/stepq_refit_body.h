@@ -234,17 +234,6 @@ __device__ __forceinline__ void refit_y_mfma(const uint32_t (&Ub)[4][4][2], Refi
 }
 
 template <int B>
-__device__ __forceinline__ void word_scale(float *Y, const float *hrow, int x0)
-{
-#pragma unroll
-    for (int s = 0; s < 8 / B; ++s) {
-        const float h = hrow[x0 + s];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) Y[4 * s + e] *= h;
-    }
-}
-
-template <int B>
 __device__ __forceinline__ void word_scale_max(float *Y, const float *hrow, int x0, float (&mx)[4])
 {
 #pragma unroll
@@ -464,7 +453,7 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
 // (generic) or tested each lane's width in each word-step (row-mix): a
 // 512-request x 16-head row-unit map with channel-wise gates 120.7 -> 98.4 us
 // (1,942 -> 1,645 instructions per wave), 201 requests x 6 heads of random
-// 2/4/8-bit rows at d_k = 96, d_v = 64 16.0 -> 14.3 us.
+// 2/4/8-bit rows at d_k = 96, d_v = 64 16.0 -> 10.9 us.
 
 // ROWMIX: the first half is the frozen row-mix body's (rowmix_sums, with its
 // own row tables in d); the slot constants are then copies of those.
@@ -516,11 +505,12 @@ __device__ __forceinline__ uint32_t requant_rows(const float *Y, const float (&g
 // The unpacked fields of the thread's rows as fp32, in the registers that
 // hold the values afterwards.
 template <int NP, bool HAS2>
-__device__ __forceinline__ void slot_fields(const SlotGeom &g, const uint32_t (&wa)[NP], const uint32_t (&wb)[NP],
+__device__ __forceinline__ void slot_fields(const SlotGeom &g, uint32_t live, const uint32_t (&wa)[NP], const uint32_t (&wb)[NP],
                                             float (&Y)[NP][8])
 {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
+        if (!(live >> p & 1u)) continue;
         uint32_t lo, hi;
         slot_views<NP, HAS2>(g, wa, wb, p, lo, hi);
 #pragma unroll
@@ -544,6 +534,14 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     const SlotGeom g(t.hi, D::NSL == 8 ? 3 : 4);
     const LevelTable lv = hold_levels(a.pool.lv);
     const SlotWords<DV> cw(t.codes, g, slice);
+    // Pairs without a row in this wave are left out of the passes: d_k = 96, d_v
+    // = 64 with rows of 2/4/8 bits at random, 201 requests x 6 heads, 14.5 -> 10.9
+    // us; 256 x 16 heads of d_k = 72, d_v = 128 37.8 -> 30.3 us; d_k = 128 59.3 ->
+    // 59.2 us.  The row-mix launches have few such pairs (9 for 8 pairs' rows;
+    // the tests cost more: 98.4 -> 101.7 us), and so have the row absmax's three
+    // passes (from 4% slower to 6% faster): those run all pairs.
+    constexpr bool kSkip = !ROWMIX && MODE == Refit::DualAxis;
+    const uint32_t live = kSkip ? live_pairs<D::NSL>(g, slice) : ~0u;
     uint32_t wa[NP], wb[NP];
     u32x16 w16;
     const int ng = g.g8 + g.g4;
@@ -600,13 +598,14 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
                 wa[p] = early ? soon : late;
             }
         }
-        slot_fields<NP, HAS2>(g, wa, wb, Y);
+        slot_fields<NP, HAS2>(g, live, wa, wb, Y);
     } else {
         const float kappa = slot_constants<DIAG>(t.hi, dk, t.alpha, t.beta, op, sh.d, lv, row);
-        slot_fields<NP, HAS2>(g, wa, wb, Y);
+        slot_fields<NP, HAS2>(g, live, wa, wb, Y);
         float acK[4] = {0.f, 0.f, 0.f, 0.f}, acQ[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
+            if (!(live >> p & 1u)) continue;
             const float4 c = *reinterpret_cast<const float4 *>(&sh.d.kq[slice][2 * p]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -637,6 +636,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     float *rowp = &sh.u.rowp[slice][cg >> 1];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
+        if (!(live >> p & 1u)) continue;
         const float2 as = *reinterpret_cast<const float2 *>(avs + 2 * p);
         const float2 ag = *reinterpret_cast<const float2 *>(als + 2 * p);
 #pragma unroll
@@ -664,6 +664,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     if constexpr (MODE == Refit::RowAbsmax) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
+            if (!(live >> p & 1u)) continue;
             const float2 h = *reinterpret_cast<const float2 *>(&sh.hrow[slice][2 * p]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -689,6 +690,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
                         mx[e] = 0.f;
                     }
                 }
+                if (!(live >> p & 1u)) continue;
                 const float2 h = *reinterpret_cast<const float2 *>(&sh.hrow[slice][2 * p]);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -712,6 +714,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
             float num[4] = {0.f, 0.f, 0.f, 0.f}, den[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
+                if (!(live >> p & 1u)) continue;
                 const float2 W = *reinterpret_cast<const float2 *>(&sh.wrow[slice][2 * p]);
                 row_fit(&Y[p][0], W.x, ec, num, den);
                 row_fit(&Y[p][4], W.y, ec, num, den);
@@ -728,6 +731,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     // pass 4: requantize on the new scales, store in place
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
+        if (!(live >> p & 1u)) continue;
         if (p < g.p4) {
             cw.st8(2 * p, requant_rows<8, 1>(&Y[p][0], gc) ^ 0x80808080u);
             cw.st8(2 * p + 1, requant_rows<8, 1>(&Y[p][4], gc) ^ 0x80808080u);

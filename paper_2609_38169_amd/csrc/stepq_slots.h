@@ -12,8 +12,8 @@
 // class's last group are out of the buffer's range) or stay 0 (empty fields).
 //
 // NP is the pairs of the launch's largest head (slot_pairs in
-// stepq_layout.h), rounded up to the next size that is compiled: the passes
-// run all NP pairs without a test.
+// stepq_layout.h), rounded up to the next size that is compiled; live_pairs
+// says which of them a wave needs.
 #pragma once
 
 #include "stepq_device.h"
@@ -53,6 +53,29 @@ struct SlotGeom {
         pt = p2 + 2 * ((g2 + r) >> nsl_shift);
     }
 };
+
+// The pairs in which this wave's slices have a row at all, one bit each: a
+// class's last word-step fills only some of the slices, and NP is that of the
+// launch's largest head.  Uniform per wave; the other pairs' slots have zero
+// constants, so leaving them out changes no sum and no maximum.
+template <int NSL>
+__device__ __forceinline__ uint32_t live_pairs(const SlotGeom &g, int slice)
+{
+    constexpr int SH = NSL == 8 ? 3 : 4, R = NSL - 1, S = NSL / 4;     // S slices per wave
+    const int s0 = __builtin_amdgcn_readfirstlane(slice);
+    const int e4 = g.g8 + g.g4, e2 = e4 + g.g2;
+    int n4 = 0, n2 = 0;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        // word-steps of slice s0 + s up to the end of each class
+        const int r = R - s0 - s;
+        const int a8 = (g.g8 + r) >> SH, a4 = (e4 + r) >> SH, a2 = (e2 + r) >> SH;
+        n4 = max(n4, a4 - a8);
+        n2 = max(n2, a2 - a4);
+    }
+    const int n8 = ((g.g8 + R - s0) >> SH) + 1;
+    return ((1u << (n8 >> 1)) - 1u) | (((1u << n4) - 1u) << g.p4) | (((1u << (2 * n2)) - 1u) << g.p2);
+}
 
 // The code words of a slot-body tile.  The slices take the row groups of the
 // whole codes region in turn (group g belongs to slice g mod NSL), so where a
