@@ -276,20 +276,20 @@ bool refit_body_runs(int code, const HeadInfo &hi, int dk)
 {
     const int L = static_cast<int>(hi.layout);
     if (compiled(code)) return L == code;    // whole FP16 heads take their decode body in every mode
-    // the row-mix class has a refitting body of its own (the dual-axis fit;
-    // the row-absmax step takes the generic body, which runs these heads too)
+    // the row-mix class runs the slot body with the row-mix first half, in the
+    // dual-axis fit and in the row-absmax step
     if (code == kRowMix) return rowmix_head(hi, dk);
     // the combined launch of the uniform refitting bodies and whole FP16 heads
     if (code == kMultiUniform) return compiled(L);
     // padded pivot heads have a refitting body of their own (the dual-axis
-    // fit; the row-absmax step takes the generic body, which runs them too),
+    // fit; the row-absmax step takes the slot bodies, which run them too),
     // which also runs the heads of their uniform layout in one launch
     if (pivot_uniform(code)) return L == code;
     if (code > kMixedPivotBase && code <= kMixedPivotBase + 2) {
         const int u = code - kMixedPivotBase;
         return L == u || L == kPivotUniformBase + u;
     }
-    // every other code runs the generic refitting body, which reads the
+    // every other code runs the slot bodies of the refit, which read the
     // head's own record (the tight layout, or a padded uniform mix)
     return !compiled(L);
 }

@@ -22,7 +22,7 @@
 // denominator.  The new r' and c' overwrite the tile's scales; a zero
 // denominator keeps c_j.
 //
-// The generic body also runs the single-axis baseline the paper compares
+// The slot bodies also run the single-axis baseline the paper compares
 // against (Section 5.1: symmetric row-wise absmax INT-b): every step
 //     r'_i = max_j |X_ij| = (r_i / q_b) max_j c_j |y_ij|,   c'_j = 1,
 //     q'_ij = clip(round(y_ij c_j r_i / r'_i), -q_b, q_b),

@@ -17,8 +17,8 @@
 //     r'_i = r_i M_i / q_b,   h_i = r_i / r'_i,   q'_ij = round(z_ij h_i),
 // one FMA (with the field bias) and the round-and-pack per element.  No
 // clamp is needed: |z_ij h_i| <= q_b up to a few ulp, and the biased value
-// rounds inside [1, 2^b - 1].  Other layouts take the generic refitting
-// body (stepq_refit_body.h).
+// rounds inside [1, 2^b - 1].  Other layouts take the slot bodies
+// (stepq_refit_body.h).
 #include "stepq_refit_body.h"
 
 namespace stepq {
