@@ -312,19 +312,22 @@ struct RowColOps {
     __device__ __forceinline__ float v() const { return act_value<BF16>(vb); }
 };
 
-// The column a thread owns in the column phases, or -1.
-template <int DV>
+// The column a thread owns in the column phases, or -1.  TOGETHER: columns on
+// waves 0 and 1, beside the rows, their operands requested once the code words
+// have arrived (columns_with_rows says for which launches).
+template <int DV, bool TOGETHER = false>
 __device__ __forceinline__ int own_column()
 {
     // whole waves: the wave's first thread decides, a scalar test
-    const int first = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) - 128;
-    return first >= 0 && first < DV ? static_cast<int>(threadIdx.x) - 128 : -1;
+    constexpr int t0 = TOGETHER ? 0 : 128;
+    const int first = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) - t0;
+    return first >= 0 && first < DV ? static_cast<int>(threadIdx.x) - t0 : -1;
 }
 
 // dk: the rows of the tile (128 in the compiled bodies).  The choice between
 // rows and columns is a scalar branch: as a lane mask, the one group's loads
 // would wait for the other's registers.
-template <bool BF16, bool DIAG, int DV>
+template <bool BF16, bool DIAG, int DV, bool TOGETHER = false>
 __device__ __forceinline__ RowColOps<BF16> load_ops(const DecodeArgs &a, int dk, int tile, int b, int hq, int h,
                                               const float *rr, const float *cc)
 {
@@ -343,7 +346,14 @@ __device__ __forceinline__ RowColOps<BF16> load_ops(const DecodeArgs &a, int dk,
             op.r = rr[tid];
             op.perm = (P.perm + static_cast<size_t>(h) * dk)[tid];
         }
-    } else if (first - 128 < DV) {
+        if (TOGETHER && first < DV) {
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): the code words and the row operands
+            __builtin_amdgcn_sched_barrier(0);
+            op.c = cc[tid];
+            op.vb = act_bits<BF16>(static_cast<const char *>(a.v) + static_cast<size_t>(tile) * DV * E, tid);
+        }
+    } else if (!TOGETHER && first - 128 < DV) {
         const unsigned j = tid - 128u;
         op.c = cc[j];
         op.vb = act_bits<BF16>(static_cast<const char *>(a.v) + static_cast<size_t>(tile) * DV * E, j);
@@ -755,7 +765,7 @@ __device__ __forceinline__ float row_constants_mfma_piv(const HeadInfo &hi, floa
 // Column sums of the per-thread partials, residual, readout, column factor
 // of the code-space update.  cj, vj: the scale and value of the column the
 // thread owns (own_column).  Ends with a barrier.
-template <int DV, class SH>
+template <int DV, bool TOGETHER = false, class SH>
 __device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta, SH &sh,
                                             float kappa, float cj, float vj);
 
@@ -772,13 +782,13 @@ __device__ __forceinline__ void column_phase(const DecodeArgs &a, int tile, floa
 }
 
 // The column phase once every thread has written its partials to sh.red.
-template <int DV, class SH>
+template <int DV, bool TOGETHER, class SH>
 __device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta, SH &sh,
                                             float kappa, float cj, float vj)
 {
     constexpr int NSL = 256 / (DV / 4);
     __syncthreads();
-    if (const int j = own_column<DV>(); j >= 0) {
+    if (const int j = own_column<DV, TOGETHER>(); j >= 0) {
         const float *rk = reinterpret_cast<const float *>(&sh.red[0][0][0]);
         const float *rq = reinterpret_cast<const float *>(&sh.red[1][0][0]);
         float sk = rk[j], sq = rq[j];

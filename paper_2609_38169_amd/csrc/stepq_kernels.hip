@@ -36,7 +36,8 @@ namespace {
 // columns, so each thread receives the 4 weighted sums of its column.
 // PIV: a padded pivot head (up to kCompactPivots FP16 pivot rows beside
 // the padded uniform mix; t.hi holds its row counts and pivot offset).
-template <bool BF16, bool DIAG, int M8, int M4, int M2, bool PIV = false>
+// TOGETHER: the waves of the columns (columns_with_rows).
+template <bool BF16, bool DIAG, int M8, int M4, int M2, bool PIV = false, bool TOGETHER = false>
 __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCtx &t, DecodeShared<128> &sh)
 {
     constexpr int M = M8 + M4 + M2;
@@ -53,7 +54,7 @@ __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCt
     PivotRegs<128, kCompactPivots> pr;
     if constexpr (PIV) pivot_load<128, kCompactPivots>(t, slice, cg, pr);
 
-    const RowColOps<BF16> op = load_ops<BF16, DIAG, 128>(a, 128, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    const RowColOps<BF16> op = load_ops<BF16, DIAG, 128, TOGETHER>(a, 128, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
     int ek, eq;
     float kappa;
     if constexpr (PIV)
@@ -67,7 +68,7 @@ __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCt
     matvec_partials(sh, slice, cg, Ub, ek, eq);
     if constexpr (PIV) pivot_partials_slice(t, slice, cg, pr, sh);
 
-    column_sums<128>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, op.c, op.v());
+    column_sums<128, TOGETHER>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, op.c, op.v());
 
     const float4 b4 = *reinterpret_cast<const float4 *>(&sh.bcol[4 * cg]);
     const float bc[4] = {b4.x, b4.y, b4.z, b4.w};
@@ -207,7 +208,7 @@ __device__ __forceinline__ void decode_rowmix(const DecodeArgs &a, const TileCtx
     }
 }
 
-template <bool BF16, bool DIAG, int L>
+template <bool BF16, bool DIAG, int L, bool TOGETHER = false>
 __device__ __forceinline__ void run_uniform(const DecodeArgs &a, TileCtx &t, int slot, DecodeShared<128> &sh)
 {
     // every tile record of layout L is (codes: 1024 bytes per word-step) + r + c
@@ -217,7 +218,7 @@ __device__ __forceinline__ void run_uniform(const DecodeArgs &a, TileCtx &t, int
     t.codes = reinterpret_cast<uint32_t *>(rec);
     t.rr = reinterpret_cast<const float *>(rec + r_off);
     t.cc = t.rr + 128;
-    decode_uniform<BF16, DIAG, u.m8, u.m4, u.m2>(a, t, sh);
+    decode_uniform<BF16, DIAG, u.m8, u.m4, u.m2, false, TOGETHER>(a, t, sh);
 }
 
 // A padded pivot head of uniform layout L: codes (1024 bytes per
@@ -277,7 +278,8 @@ __device__ __forceinline__ void run_generic(const DecodeArgs &a, TileCtx &t, int
 // pivot heads only.  LAYOUT == kPivotUniformBase + L: padded pivot heads of
 // uniform layout L only.  LAYOUT == kF16HeadLayout: heads held entirely in FP16 (every mode;
 // the host sets a.f16_c_one for the row-absmax step).
-template <int DV, bool BF16, int LAYOUT, bool DIAG>
+// TOGETHER (uniform layouts): the waves of the columns (columns_with_rows).
+template <int DV, bool BF16, int LAYOUT, bool DIAG, bool TOGETHER = false>
 __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
 {
     __shared__ DecodeShared<DV> sh;
@@ -316,7 +318,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
     } else if constexpr (DV == 128 && LAYOUT == kRowMix) {
         run_rowmix<BF16, DIAG>(a, t, slot, sh);
     } else if constexpr (DV == 128 && LAYOUT > 0 && LAYOUT <= kNumUniformLayouts) {
-        run_uniform<BF16, DIAG, LAYOUT>(a, t, slot, sh);
+        run_uniform<BF16, DIAG, LAYOUT, TOGETHER>(a, t, slot, sh);
     } else if constexpr (DV == 128 && LAYOUT == kF16HeadLayout) {
         run_f16head<BF16, DIAG>(a, t, slot, sh);
     } else if constexpr (DV == 128 && LAYOUT > kPivotUniformBase) {
@@ -386,9 +388,32 @@ __global__ __launch_bounds__(256) void stream_ref_kernel(DecodeArgs a, uint32_t 
     if (tid < P.dv) a.o[static_cast<size_t>(t.tile) * P.dv + tid] = acc * __uint_as_float(zero);
 }
 
+// Whether a frozen-scale launch of one uniform layout has its columns on the
+// waves of the rows (load_ops).  On waves of their own, and requested at once,
+// every tile is done sooner and short launches gain (64 rows @8 and 64 @4,
+// 32 requests x 32 heads: 8.45 us together, 7.90 apart; 130 requests 23.5 and
+// 22.9), layouts 2 and 4 at every length (204 requests of layout 2 28.5 and
+// 27.1).  Layouts 1 and 5 lose in two ranges.  With one residency round (2,048
+// workgroups) nearly full or a few tiles over, tiles that end in step start the
+// second round late: layout 1, 66 requests 13.4 and 14.4 us, 84 requests 16.3
+// and 17.2.  Beyond four rounds of slots in drawn order: layout 1, 512 requests
+// 74.7 and 75.3; layout 5, 350 requests 38.5 and 39.0 (adjacent slots gain:
+// layout 1, 500 requests 69.8 and 68.5).  Layout 3 is the same either way.
+inline bool columns_with_rows(const DecodeArgs &a, int layout)
+{
+    if (layout != 1 && layout != 5) return false;
+    const int64_t tiles = static_cast<int64_t>(a.batch) * a.n_heads;
+    return tiles > 8192 ? a.launch_order == 0 : tiles > 1536 && tiles <= 3072;
+}
+
 template <bool BF16, bool DIAG>
 hipError_t launch_decode_128(const DecodeArgs &a, int layout, unsigned grid, hipStream_t s)
 {
+    if (columns_with_rows(a, layout)) {
+        if (layout == 1) hipLaunchKernelGGL((decode_kernel<128, BF16, 1, DIAG, true>), dim3(grid), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((decode_kernel<128, BF16, 5, DIAG, true>), dim3(grid), dim3(256), 0, s, a);
+        return hipGetLastError();
+    }
     switch (layout) {
     case 1: hipLaunchKernelGGL((decode_kernel<128, BF16, 1, DIAG>), dim3(grid), dim3(256), 0, s, a); break;
     case 2: hipLaunchKernelGGL((decode_kernel<128, BF16, 2, DIAG>), dim3(grid), dim3(256), 0, s, a); break;
