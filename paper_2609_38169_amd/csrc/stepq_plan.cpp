@@ -276,8 +276,8 @@ bool refit_body_runs(int code, const HeadInfo &hi, int dk)
 {
     const int L = static_cast<int>(hi.layout);
     if (compiled(code)) return L == code;    // whole FP16 heads take their decode body in every mode
-    // the row-mix class runs the slot body with the row-mix first half, in the
-    // dual-axis fit and in the row-absmax step
+    // the row-mix class runs a slot body of its own, in the dual-axis fit (with
+    // the frozen row-mix body's first half) and in the row-absmax step
     if (code == kRowMix) return rowmix_head(hi, dk);
     // the combined launch of the uniform refitting bodies and whole FP16 heads
     if (code == kMultiUniform) return compiled(L);
