@@ -216,29 +216,37 @@ constexpr float kMagic = 0x1.8p+23f;     // 1.5 2^23: x + this has x rounded to 
 // 1 / (r c) lie within 2^-124 .. 2^124.
 constexpr float kScaleLo = 0x1p-62f, kScaleHi = 0x1p+62f;
 
-// Codes of 4 columns of a row: round(x iq / (r c)) to +-q_b, as bytes.  The
-// quotient is formed from the reciprocals' product and one residual step
-// (which lands on the division's value but for rare last-bit cases; infinite
-// and NaN states come out as with the division); scales outside the plain
-// range take the division.
+// A quotient this close to a half (0.5 - 2^-14 from its code) is divided again.
+constexpr float kNearHalf = 0.49993896484375f;
+
+// Codes of 4 columns of a row: round(x iq / (r c)) to +-q_b, as bytes, from the
+// division's correctly rounded quotient.  Away from the halves any quotient
+// close to it gives the same code: the reciprocals' product, within
+// 3.5 2^-23 of 1 / (r c), and one residual step are within 2^-23 |y| <= 2^-16
+// of the division's value where |y| <= q_b (the residual's own rounding
+// below the normal range adds at most 2^-26).  Quotients near a half and
+// scales outside the plain range take the division; infinite and NaN states
+// come out as with it.
 __device__ __forceinline__ uint32_t quantize4(f32x4_any x, float iq, float qb, float r, float ir, bool plain,
                                               const float (&c)[4], const float (&ic)[4])
 {
-    uint32_t t[4];
+    float y[4];
+    bool divide = !plain;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float num = x[e] * iq, rc = r * c[e];
-        float y;
-        if (plain) {
-            const float inv = ir * ic[e];
-            const float q0 = __builtin_amdgcn_fmed3f(num * inv, -256.0f, 256.0f);
-            y = fmaf(fmaf(-q0, rc, num), inv, q0);
-        } else {
-            y = num / rc;
-        }
-        y = fminf(fmaxf(y, -qb), qb);
-        t[e] = __float_as_uint(y + kMagic);
+        const float inv = ir * ic[e];
+        const float q0 = __builtin_amdgcn_fmed3f(num * inv, -256.0f, 256.0f);
+        y[e] = fminf(fmaxf(fmaf(fmaf(-q0, rc, num), inv, q0), -qb), qb);
+        divide = divide || fabsf(y[e] - ((y[e] + kMagic) - kMagic)) > kNearHalf;
     }
+    if (divide) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = fminf(fmaxf((x[e] * iq) / (r * c[e]), -qb), qb);
+    }
+    uint32_t t[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = __float_as_uint(y[e] + kMagic);
     // the low bytes
     return __builtin_amdgcn_perm(__builtin_amdgcn_perm(t[3], t[2], 0x0c0c0400u), __builtin_amdgcn_perm(t[1], t[0], 0x0c0c0400u),
                                  0x05040100u);

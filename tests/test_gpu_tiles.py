@@ -70,12 +70,7 @@ def test_tile_ops_plain_formulas(dk, dv, levels):
     torch.cuda.synchronize()
     assert torch.equal(image, pool.memory)
     got = gc.cpu().numpy()
-    off = got != codes
-    if off.any():
-        # another last bit of the quotient than the division's may only show where the value is a half
-        with np.errstate(all="ignore"):
-            yd = (S.astype(np.float64) * iq[None, :, :, None]) / (r[..., None].astype(np.float64) * c[:, :, None, :])
-        assert np.abs(np.abs(yd[off] - np.floor(yd[off])) - 0.5).max() < 1e-5, np.argwhere(off)[:5]
+    assert np.array_equal(got, codes), np.argwhere(got != codes)[:5]
     assert np.array_equal(gr.cpu().numpy(), r) and np.array_equal(gcol.cpu().numpy(), c)
     want_p = np.where(integer, np.float16(0), half).view(np.int16)
     nan = np.isnan(np.where(integer, np.float16(0), half))
@@ -84,3 +79,56 @@ def test_tile_ops_plain_formulas(dk, dv, levels):
         want = np.where(integer, (r[..., None] * c[:, :, None, :]) * (got.astype(np.float32) / iq[None, :, :, None]),
                         half.astype(np.float32))
     assert np.array_equal(deq.cpu().numpy(), want, equal_nan=True)
+
+
+def _hard_quotients():
+    """(num, r, c), r c = den exactly, of 24 significant bits, whose quotient num / den lies within 2^-42 of the
+    midpoint of a half code and the fp32 value beside it, so that a quotient with
+    one wrong last bit gives another code.  With the midpoint M / 2^s, M odd of 25
+    bits, den = d / M mod 2^t makes den M = num 2^t + d."""
+    out = []
+    for m in range(127):
+        for side in (-1, 1):
+            h = np.float32(m + 0.5)
+            beside = np.nextafter(h, np.float32(side * 1000))
+            M, s = (float(h) + float(beside)) / 2, 0
+            while M < 2 ** 24 or M != int(M):
+                M, s = M * 2, s + 1
+            M = int(M)
+            for t in (24, 25, 26):
+                inv = pow(M, -1, 2 ** t)
+                for d in [x for a in range(1, 33) for x in (-a, a)]:
+                    den = d * inv % 2 ** t
+                    num = (den * M - d) >> t
+                    f = [f for f in (3, 5, 7, 11, 13, 17, 19) if den % f == 0]
+                    if 2 ** 23 <= den < 2 ** 24 and 0 < num < 2 ** 24 and f:
+                        out.append((num * 2.0 ** (t - s), float(den // f[-1]), float(f[-1])))
+    return np.array(out)
+
+
+def test_pack_rounds_the_divisions_quotient():
+    """The codes are those of the correctly rounded quotient, also where the
+    exact one is as close to the rounding boundary as 24-bit operands allow."""
+    hard = _hard_quotients()
+    dk = dv = 128
+    rows = []
+    for f in np.unique(hard[:, 2]):
+        x = hard[hard[:, 2] == f]
+        rows += [x[i:i + dk] for i in range(0, len(x) - dk + 1, dk)]
+    hard = np.stack(rows)[:, None]                                 # [n][1][dk][3], one c factor per tile
+    n = len(hard)
+    e = np.exp2(np.arange(dv) // 2 % 16 - 8.0) * np.where(np.arange(dv) % 2, -1.0, 1.0)
+    r = (hard[..., 1] * 2.0 ** -24).astype(np.float32)
+    c = (hard[:, :, :1, 2] * np.abs(e)).astype(np.float32)
+    S = ((hard[..., 0] * 2.0 ** -24)[..., None] * e).astype(np.float32)
+    assert np.array_equal(S.astype(np.float64), (hard[..., 0] * 2.0 ** -24)[..., None] * e)
+    y = S / (r[..., None] * c[:, :, None, :])
+    want = np.clip(np.rint(y), -127, 127).astype(np.int8)
+    print(f"hard quotients: {n * dk} rows", flush=True)
+    pool = stepq.Pool(n, 1, 1, dk, dv, np.full((1, dk), 8, np.uint8), device=DEV, levels=1)
+    ids = torch.arange(n, dtype=torch.int32, device=DEV)
+    pool.load(ids, *(torch.from_numpy(np.ascontiguousarray(a)).to(DEV) for a in (S, r, c)))
+    got = torch.empty((n, 1, dk, dv), dtype=torch.int8, device=DEV)
+    pool.export(ids, got, torch.empty((n, 1, dk), device=DEV), torch.empty((n, 1, dv), device=DEV))
+    off = got.cpu().numpy() != want
+    assert not off.any(), (int(off.sum()), np.argwhere(off)[:5])
