@@ -541,6 +541,12 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     // the tests cost more: 98.4 -> 101.7 us), and so have the row absmax's three
     // passes (from 4% slower to 6% faster): those run all pairs.
     constexpr bool kSkip = !ROWMIX && MODE == Refit::DualAxis;
+    // Without those branches the weights of later pairs are read ahead into
+    // registers.  Kept in order where that crosses a step of occupancy: at 10
+    // pairs (spills at 4 waves per SIMD; d_k = 120 rows @8 / @4, 256 x 16 heads
+    // 40.9 -> 34.5 us), at 4 with the scalar gate (7 waves; d_k = d_v = 64, 400 x
+    // 12 heads 19.5 -> 17.5 us); elsewhere it is 1 to 5% slower.
+    constexpr bool kInOrder = MODE == Refit::RowAbsmax && (NP == 10 || (NP == 4 && !DIAG));
     const uint32_t live = kSkip ? live_pairs<D::NSL>(g, slice) : ~0u;
     uint32_t wa[NP], wb[NP];
     u32x16 w16;
@@ -600,7 +606,10 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
         }
         slot_fields<NP, HAS2>(g, live, wa, wb, Y);
     } else {
-        const float kappa = slot_constants<DIAG>(t.hi, dk, t.alpha, t.beta, op, sh.d, lv, row);
+        // in scalar registers once they have come: held as loaded, two vector
+        // registers more make the launch bounds spill
+        const float alpha = uniform_f(t.alpha), beta = uniform_f(t.beta);
+        const float kappa = slot_constants<DIAG>(t.hi, dk, alpha, beta, op, sh.d, lv, row);
         slot_fields<NP, HAS2>(g, live, wa, wb, Y);
         float acK[4] = {0.f, 0.f, 0.f, 0.f}, acQ[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -612,11 +621,12 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
                 acK[e] = fmaf(c.z, Y[p][4 + e], fmaf(c.x, Y[p][e], acK[e]));
                 acQ[e] = fmaf(c.w, Y[p][4 + e], fmaf(c.y, Y[p][e], acQ[e]));
             }
+            if constexpr (kInOrder) __builtin_amdgcn_sched_barrier(0);
         }
         pivot_acc(t, slice, cg, pr, sh.d, acK, acQ);
         sh.d.red[0][slice][cg] = make_float4(acK[0], acK[1], acK[2], acK[3]);
         sh.d.red[1][slice][cg] = make_float4(acQ[0], acQ[1], acQ[2], acQ[3]);
-        column_sums<DV>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh.d, kappa, sh.d.cpiv[tid & (DV - 1)],
+        column_sums<DV>(a, t.tile, DIAG ? 1.0f : alpha, beta, sh.d, kappa, sh.d.cpiv[tid & (DV - 1)],
                         sh.d.bcol[tid & (DV - 1)]);
     }
 
@@ -772,7 +782,7 @@ __device__ __forceinline__ void run_refit_uniform_piv(const DecodeArgs &a, TileC
 // compiled layouts).
 // The slot bodies' second bound is the waves per SIMD that their 8 NP values
 // leave room for; without it the compiler takes a few registers more than the
-// next step of occupancy.
+// next step of occupancy.  No body spills under it.
 constexpr int refit_waves(int np) { return np == 0 ? 1 : (np <= 6 ? 5 : (np <= 10 ? 4 : 3)); }
 
 template <int DV, bool BF16, int LAYOUT, bool DIAG, Refit MODE, int NP = 0>
