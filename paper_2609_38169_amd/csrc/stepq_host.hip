@@ -95,18 +95,25 @@ stepq::PoolView make_view(const stepq_pool *p)
     return v;
 }
 
-// How far each request's heads are rotated in a launch with a head list.  Up
-// to 2,048 tiles (8 workgroups on each of 256 CUs) run at once, so a CU with
-// more of the heavy heads ends the launch late: the golden section of n spreads
-// every CU's tiles evenly over the list (64 requests x 16 heads @8 and 16 @4,
-// fp32 activations: 14.1 -> 12.9 us).  In longer launches the dispatcher
-// evens the load out, and neighbouring requests starting one head apart stream
-// a little better (512 requests x 32 heads with one FP16 head: 79.4 us, 80.7
-// with the golden section).
-int32_t head_rotation(int32_t batch, int32_t n)
+// How far each request's heads are rotated from the last one's in a launch over
+// the pool's head list.  A frozen combined launch of 5 to 8 tiles a CU runs all its
+// workgroups at once (7 or 8 fit a CU), so a CU with more of the heavy heads
+// ends the launch late: those launches take the rotation that spreads every
+// CU's tiles best (stepq_plan.h).  Rotation by one, by the golden section of n
+// and this one: 64 requests x 32 heads, half @8 and half @4, 13.5, 12.7 and 12.5
+// us; 40 x 48 13.7, 13.4 and 12.9; 200 x 10 13.2, 14.2 and 13.3; 96 x 20 with an
+// FP16 head 15.7, 17.1 and 15.6.  With fewer tiles no rotation shows (32 x 32
+// 8.5 and 8.5 us; the refit, at most 4 tiles a CU, 12.6 and 12.6).  In longer
+// launches the dispatcher evens the load out, and neighbouring requests one
+// head apart stream a little better (512 requests x 32 heads with one FP16
+// head: 79.4 us, with the golden section 80.7).  Launches of one class have
+// heads of one kind.
+int32_t head_rotation(const stepq_pool *p, const stepq::DecodeArgs &a, bool refit)
 {
-    if (static_cast<int64_t>(batch) * n > 2048) return 1;
-    return static_cast<int32_t>(0.6180339887 * n + 0.5);
+    const int64_t tiles = static_cast<int64_t>(a.batch) * a.n_heads;
+    const int64_t k = (tiles + stepq::kCus - 1) / stepq::kCus - stepq::kRotFirst;
+    if (refit || p->plan.mixed_code == 0 || k < 0 || k >= stepq::kRotTiles) return 1;
+    return p->plan.rot[a.launch_order != 0 || tiles % 8 != 0][k];
 }
 
 bool debug_checks()
@@ -357,7 +364,7 @@ static stepq_status decode_step_impl(stepq_pool *p, const int32_t *slot_ids, int
     a.launch_order = (flags & STEPQ_STEP_ADJACENT_SLOTS) ? 1 : 0;
     int pairs = p->plan.pairs;
     auto launch = [&](int layout) {
-        a.head_rot = head_rotation(a.batch, a.n_heads);
+        a.head_rot = head_rotation(p, a, flags & (STEPQ_STEP_REFIT | STEPQ_STEP_ROW_ABSMAX));
         if (layout == stepq::kF16HeadLayout) {
             // whole FP16 heads: no integer rows to fit, so every mode is the same update
             a.f16_c_one = (flags & STEPQ_STEP_ROW_ABSMAX) ? 1 : 0;
@@ -450,7 +457,7 @@ stepq_status stepq_decode_stream_ref(stepq_pool *p, const int32_t *slot_ids, int
     a.head_list = p->plan.order.empty() ? nullptr : p->d_head_order;
     a.n_heads = p->Hv;
     a.div_heads = p->div_hv;
-    a.head_rot = head_rotation(a.batch, a.n_heads);
+    a.head_rot = head_rotation(p, a, false);
     const hipError_t e = stepq::launch_stream_ref(a, act_dtype == STEPQ_BF16, s);
     return e == hipSuccess ? STEPQ_OK : hip_fail(e, "reference launch");
 }

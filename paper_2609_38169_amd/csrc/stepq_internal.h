@@ -36,7 +36,7 @@ struct DecodeArgs {
     const void *q, *k, *v, *alpha, *beta;
     float *o;
     int32_t batch;
-    int32_t head_rot;        // heads of head_list that each request's order is rotated by (below n_heads)
+    int32_t head_rot;        // heads of head_list that each request's order is rotated by from the last one's
     // The value heads one launch covers: head_list[0 .. n_heads) (device),
     // or every head 0 .. Hv-1 in order when head_list is NULL (then every
     // head has the same tile size).  The grid is batch x n_heads workgroups.

@@ -105,6 +105,16 @@ constexpr int slot_pairs_compiled(int pairs, int dv)
     return pairs <= 6 ? 6 : (pairs <= 8 ? 8 : (pairs <= 10 ? 10 : kSlotPairsAny));
 }
 
+// Tiles that one CU gets in a launch of one residency round: the 256 CUs take
+// the launch's tiles in turn, kFlatStride apart where tile l is workgroup l,
+// and kRunStride apart where the XCDs take runs of tiles (stepq_device.h,
+// tile_of).  From kRotFirst to kRotFirst + kRotTiles - 1 tiles, a combined
+// launch's heads are rotated so that no CU gets more than its share of the
+// heavy ones (stepq_plan.h, best_rotation).
+constexpr int kCus = 256;
+constexpr int kRunStride = kCus / 8, kFlatStride = kCus;
+constexpr int kRotFirst = 5, kRotTiles = 4;
+
 // One value head of a decode launch over part of a pool's heads: its index
 // and the byte offset of its tile within a slot record.
 struct LaunchHead {

@@ -241,6 +241,52 @@ void plan_launches(const std::vector<HeadInfo> &heads, int dk, int dv, LaunchPla
         plan->mixed_code = piv ? kMultiPivot : kMultiUniform;
     else if (fits && L != 0 && others > 0)
         plan->mixed_code = (f16 ? kMixedF16Base : kMixedBase) + L;
+    if (plan->mixed_code == 0) return;
+    for (int k = 0; k < kRotTiles; ++k) {
+        plan->rot[0][k] = best_rotation(static_cast<int>(heads.size()), kRunStride, kRotFirst + k);
+        plan->rot[1][k] = best_rotation(static_cast<int>(heads.size()), kFlatStride, kRotFirst + k);
+    }
+}
+
+HeadSpread head_spread(int n, int rot, int stride, int tiles, int enough)
+{
+    std::vector<int> at(tiles);
+    HeadSpread r{0, 0};
+    for (int l0 = 0; l0 < n && r.worst <= enough; ++l0) {       // later starts repeat these, all entries moved by rot
+        for (int k = 0; k < tiles; ++k) {
+            const int l = l0 + k * stride, b = l / n;
+            at[k] = (l - b * n + b * rot) % n;
+        }
+        std::sort(at.begin(), at.end());
+        // n (tiles among the first entries) - tiles (entries): at its least
+        // before a tile's entry, at its most after it
+        int lo = 0, hi = 0;
+        for (int k = 0; k < tiles; ++k) {
+            lo = std::min(lo, n * k - tiles * at[k]);
+            if (k + 1 == tiles || at[k + 1] != at[k]) hi = std::max(hi, n * (k + 1) - tiles * (at[k] + 1));
+        }
+        r.worst = std::max(r.worst, hi - lo);
+        r.sum += hi - lo;
+    }
+    return r;
+}
+
+int best_rotation(int n, int stride, int tiles)
+{
+    const int golden = static_cast<int>(0.6180339887 * n + 0.5) % n;
+    if (n > 128) return golden;            // long lists: a CU's few tiles are far apart anyway
+    int best = 1 % n;
+    HeadSpread least = head_spread(n, best, stride, tiles);
+    for (int d = 0; d < n; ++d)
+        for (int rot : {golden - d, golden + d}) {
+            if (rot < 0 || rot >= n) continue;
+            const HeadSpread s = head_spread(n, rot, stride, tiles, least.worst);
+            if (s.worst < least.worst || (s.worst == least.worst && s.sum < least.sum)) {
+                least = s;
+                best = rot;
+            }
+        }
+    return best;
 }
 
 bool decode_body_runs(int code, const HeadInfo &hi, int dk)

@@ -30,6 +30,10 @@ struct LaunchPlan {
     std::vector<LaunchHead> order;
     std::vector<int> cls_code, cls_off, cls_cnt;
     int mixed_code = 0;
+    // rotation of the combined launch's heads from request to request, by the
+    // distance of a CU's tiles (0: kRunStride, 1: kFlatStride) and their number
+    // (kRotTiles first); 1 in all other launches
+    int rot[2][kRotTiles] = {{1, 1, 1, 1}, {1, 1, 1, 1}};
     // the most slot_pairs of a head: of the whole pool, and per class
     int pairs = 0;
     std::vector<int> cls_pairs;
@@ -55,6 +59,21 @@ bool refit_combined(int mixed_code);
 // Tile size that the compiled body of layout code L (1 .. kF16HeadLayout)
 // assumes for every head when it runs without a head list; 0 otherwise.
 uint32_t fixed_tile_bytes(int layout);
+
+// The most that the tiles l0, l0 + stride, ..., `tiles` of them, lean to one
+// run of an n-entry head list when every request's heads are rotated by rot
+// from the last one's: the largest difference, over all runs of consecutive
+// entries (around the end), between the tiles in the run and its even share,
+// times n.  The worst l0, and the sum over all.  Once the worst is past
+// `enough` the exact values do not matter.
+struct HeadSpread {
+    int worst, sum;
+};
+HeadSpread head_spread(int n, int rot, int stride, int tiles, int enough = INT32_MAX);
+
+// The rotation 0 <= rot < n with the least head_spread, worst before sum; of
+// several, one, or else the nearest to the golden section of n.
+int best_rotation(int n, int stride, int tiles);
 
 // Check a plan against the head records before anything is launched with it:
 //  - the head records tile the slot record: consecutive tiles, each region

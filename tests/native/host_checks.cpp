@@ -171,6 +171,39 @@ void check_fast_div()
     }
 }
 
+// Rotations of a combined launch's heads: the spread by counting the tiles in
+// every run of list entries, and no rotation by one or by the golden section
+// better than the chosen one.
+void check_rotations()
+{
+    for (int n = 1; n <= 64; ++n)
+        for (int stride : {stepq::kRunStride, stepq::kFlatStride})
+            for (int k = 0; k < stepq::kRotTiles; ++k) {
+                const int tiles = stepq::kRotFirst + k;
+                const int rot = stepq::best_rotation(n, stride, tiles);
+                expect(rot >= 0 && rot < n, "rotation outside the list", std::to_string(n));
+                int worst = 0;
+                for (int l0 = 0; l0 < n; ++l0) {
+                    std::vector<int> at(n, 0);
+                    for (int t = 0; t < tiles; ++t) {
+                        const int l = l0 + t * stride, b = l / n;
+                        ++at[(l % n + b * rot) % n];
+                    }
+                    for (int first = 0; first < n; ++first)
+                        for (int len = 1, in = 0; len <= n; ++len) {
+                            in += at[(first + len - 1) % n];
+                            worst = std::max(worst, std::abs(n * in - tiles * len));
+                        }
+                }
+                const std::string at = std::to_string(n) + " heads, " + std::to_string(tiles) + " tiles";
+                const int spread = stepq::head_spread(n, rot, stride, tiles).worst;
+                expect(spread == worst, "spread of a rotation", at);
+                expect(spread <= stepq::head_spread(n, 1 % n, stride, tiles).worst, "rotation by one spreads better", at);
+                const int golden = static_cast<int>(0.6180339887 * n + 0.5) % n;
+                expect(spread <= stepq::head_spread(n, golden, stride, tiles).worst, "the golden section spreads better", at);
+            }
+}
+
 void check_setup()
 {
     Rng g(3);
@@ -270,6 +303,7 @@ int main()
 {
     check_plans();
     check_fast_div();
+    check_rotations();
     check_setup();
     if (g_failures) {
         std::fprintf(stderr, "%d failed expectations\n", g_failures);

@@ -66,3 +66,22 @@ def test_waves_of_the_columns(layout, kda, bf16):
             pool.memory.copy_(start)
             got = _run(pool, ids, x, kda, [(0, B)], adjacent)
             assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (B, adjacent)
+
+
+@pytest.mark.parametrize("adjacent", [False, True])
+@pytest.mark.parametrize("Hv", [6, 20, 32])
+def test_rotation_of_combined_launches(Hv, adjacent):
+    """Heads @8 and @4 in one combined launch: 4, 5 and 8 tiles a CU, and one
+    request more than a residency round, each also in parts."""
+    bits = np.stack([np.full(128, 8 if h % 2 else 4, np.uint8) for h in range(Hv)])
+    top = 2048 // Hv
+    for B in (1024 // Hv, 1024 // Hv + 1, top, top + 1):
+        print(f"rotation Hv={Hv} B={B} adjacent={adjacent}", flush=True)
+        x = _inputs(B, Hv, Hv // 2, False, False, B)
+        ids = torch.arange(B, dtype=torch.int32, device=DEV)
+        pool = _pool(bits, B, Hv // 2, B)
+        start = pool.memory.clone()
+        want = _run(pool, ids, x, False, [(lo, min(B, lo + 16)) for lo in range(0, B, 16)])
+        pool.memory.copy_(start)
+        got = _run(pool, ids, x, False, [(0, B)], adjacent)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), B
