@@ -55,6 +55,12 @@ __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCt
     if constexpr (PIV) pivot_load<128, kCompactPivots>(t, slice, cg, pr);
 
     const RowColOps<BF16> op = load_ops<BF16, DIAG, 128, TOGETHER>(a, 128, t.tile, t.b, t.hq, t.h, t.rr, t.cc);
+    // with fp32 activations a pivot head's v_j and c_j wait in LDS, not in
+    // registers: 63 of them, not 65, so 8 waves per SIMD, not 7 (62 requests x 32
+    // heads with pivot rows in all: 14.6 -> 13.9 us; 400 requests 65.1 -> 65.9).
+    // With bf16 the scalar gate fits without it, and the channel-wise one gains nothing.
+    constexpr bool kColumnsWait = PIV && !BF16;
+    if (kColumnsWait && own_column<128>() >= 0) sh.bcol[tid - 128] = op.v();
     int ek, eq;
     float kappa;
     if constexpr (PIV)
@@ -68,7 +74,8 @@ __device__ __forceinline__ void decode_uniform(const DecodeArgs &a, const TileCt
     matvec_partials(sh, slice, cg, Ub, ek, eq);
     if constexpr (PIV) pivot_partials_slice(t, slice, cg, pr, sh);
 
-    column_sums<128, TOGETHER>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, op.c, op.v());
+    column_sums<128, TOGETHER>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa,
+                               kColumnsWait ? sh.cpiv[tid & 127] : op.c, kColumnsWait ? sh.bcol[tid & 127] : op.v());
 
     const float4 b4 = *reinterpret_cast<const float4 *>(&sh.bcol[4 * cg]);
     const float bc[4] = {b4.x, b4.y, b4.z, b4.w};

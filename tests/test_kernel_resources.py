@@ -52,3 +52,13 @@ def test_no_kernel_uses_scratch():
     bad = {k[".name"]: (k[".private_segment_fixed_size"], k[".vgpr_spill_count"])
            for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]}
     assert not bad, bad
+
+
+def test_frozen_bodies_keep_eight_waves():
+    """The frozen steps' bodies for fp32 activations at d_v = 128, but for the
+    one of any mix (layout 0), fit 64 registers: 8 waves per SIMD, on which a
+    launch's rounds rest."""
+    stepq.lib()
+    wide = {k[".name"]: k[".vgpr_count"] for k in _kernels()
+            if "decode_kernelILi128ELb0E" in k[".name"] and "ELi0ELb" not in k[".name"] and k[".vgpr_count"] > 64}
+    assert not wide, wide
