@@ -47,12 +47,20 @@ def device_targets(path: str) -> list[str]:
     return sorted(set(t.decode() for t in re.findall(rb"hipv4-amdgcn-amd-amdhsa--(gfx[0-9a-f]+)", data)))
 
 
-def args_command(out: str, csrc: str) -> list[str]:
-    import torch
-    from torch.utils.cpp_extension import include_paths
+def args_command(out: str, csrc: str) -> list[str] | None:
+    """The command that builds the binding's native checks, or None without
+    Python's and torch's headers (the library needs neither)."""
+    try:
+        import torch
+        from torch.utils.cpp_extension import include_paths
+    except ImportError:
+        return None
     tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    inc = [f for d in include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
-           for f in ("-I", d)]
+    py = sysconfig.get_paths()["include"]
+    if not (os.path.exists(os.path.join(py, "Python.h"))
+            and any(os.path.exists(os.path.join(d, "ATen", "core", "Tensor.h")) for d in include_paths())):
+        return None
+    inc = [f for d in include_paths() + [py, os.path.join(ROOT, "include")] for f in ("-I", d)]
     return (["g++"] + CXX_FLAGS + ["-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}"] + inc
             + [os.path.join(csrc, ARGS_SOURCE), "-o", out, "-L", tlib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"])
 
@@ -83,8 +91,16 @@ def build(extra_flags: list[str] | None = None, out: str = LIB, verbose: bool = 
         o = os.path.join(build_dir, s + ".o")
         cmds.append(["g++"] + CXX_FLAGS + inc + ["-c", os.path.join(csrc, s), "-o", o])
         objs.append(o)
-    if out == LIB:
-        cmds.append(args_command(ARGS_MODULE + ".tmp", csrc))
+    # the module belongs to the package, not to one library: a library of
+    # another name is used through it too
+    module = args_command(ARGS_MODULE + ".tmp", csrc) if out == LIB or not os.path.exists(ARGS_MODULE) else None
+    if module is not None:
+        cmds.append(module)
+    elif out == LIB:
+        print(f"{ARGS_MODULE}: not built (no Python or torch headers); the binding checks arguments in Python",
+              file=sys.stderr)
+        if os.path.exists(ARGS_MODULE):
+            os.remove(ARGS_MODULE)      # of an earlier build, perhaps against another torch
     # the translation units are independent: compile them side by side
     with ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as ex:
         for f in [ex.submit(run, c) for c in cmds]:
@@ -97,7 +113,7 @@ def build(extra_flags: list[str] | None = None, out: str = LIB, verbose: bool = 
         os.remove(tmp)
         raise RuntimeError(f"libstepq device bundle targets {targets}, expected only {ARCH}")
     os.replace(tmp, out)
-    if out == LIB:
+    if module is not None:
         os.replace(ARGS_MODULE + ".tmp", ARGS_MODULE)
     return out
 

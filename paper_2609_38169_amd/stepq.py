@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import numpy as np
 import torch
@@ -53,12 +54,12 @@ class stepq_pool_desc(ctypes.Structure):
 
 
 _lib = None
-_native = None      # the _stepq_args module, bound to the library's calls by lib()
+_native = None      # the _stepq_args module, bound to the library's calls by native()
 
 
 def lib():
     """The loaded library.  Raises if it has not been built."""
-    global _lib, _native
+    global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: build it with paper_2609_38169_amd.build.build()")
@@ -100,13 +101,34 @@ def lib():
             fn = getattr(L, name)
             fn.argtypes = args
             fn.restype = res
+        _lib = L
+    return _lib
+
+
+class _PythonChecks:
+    """In the native module's place where the library was built without it:
+    every device call goes through the checks below."""
+    plain = staticmethod(lambda *a: None)
+    decode = scaled = tiles = staticmethod(lambda *a: -1)
+
+
+def native():
+    """The native argument checks of the device calls, bound to the library's
+    calls (needed by pools only: the host-side calls go without)."""
+    global _native
+    if _native is None:
+        if not os.path.exists(os.path.join(_HERE, "_stepq_args.so")):
+            warnings.warn("_stepq_args.so is missing (built where Python's and torch's headers are): device calls take "
+                          "a few microseconds more", stacklevel=3)
+            _native = _PythonChecks
+            return _native
         from . import _stepq_args
-        _stepq_args.bind(*(ctypes.cast(getattr(L, name), P).value for name in (
+        L = lib()
+        _stepq_args.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
             "stepq_decode_step_ex", "stepq_pool_load", "stepq_pool_import", "stepq_pool_export", "stepq_pool_dequant",
             "stepq_pool_export_pivots", "stepq_pool_import_pivots")), torch._C._cuda_getCurrentRawStream)
         _native = _stepq_args
-        _lib = L
-    return _lib
+    return _native
 
 
 def _check(status: int):
@@ -190,7 +212,7 @@ class Pool:
         self.handle = h
         # what the native checks compare with (a device without an index matches no tensor, as in _dev)
         index = -1 if self.device.index is None else self.device.index
-        self._plain = _native.plain(h.value, index, n_v_heads, n_qk_heads, d_k, d_v)
+        self._plain = native().plain(h.value, index, n_v_heads, n_qk_heads, d_k, d_v)
 
     def close(self):
         self._plain = None
