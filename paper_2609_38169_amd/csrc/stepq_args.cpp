@@ -28,7 +28,8 @@ struct Entry {
     decltype(&stepq_pool_dequant) dequant;
     decltype(&stepq_pool_export_pivots) export_pivots;
     decltype(&stepq_pool_import_pivots) import_pivots;
-    PyObject *raw_stream;      // torch's raw current-stream query
+    int (*get_device)(int *);                  // the runtime's current device
+    PyObject *raw_stream, *stream_type;        // torch's raw current-stream query and stream class
 } g{};
 
 struct Plain {
@@ -58,17 +59,25 @@ bool take_ids(PyObject *o, const Plain &p, int64_t *n, void **out)
     return *n <= INT32_MAX && take(o, p, at::kInt, {*n}, out);
 }
 
-// None: torch's current stream; an int: the stream itself; a torch stream.
-bool take_stream(PyObject *o, const Plain &p, void **out)
+// None: torch's current stream, which is the current device's (not the pool's);
+// an int: the stream itself; a torch stream.
+bool take_stream(PyObject *o, void **out)
 {
     PyObject *v = nullptr;
     if (o == Py_None) {
-        v = PyObject_CallFunction(g.raw_stream, "i", p.device);
+        int device;
+        if (g.get_device(&device) != 0) return false;
+        if (PyObject *d = PyLong_FromLong(device)) {
+            v = PyObject_CallOneArg(g.raw_stream, d);
+            Py_DECREF(d);
+        }
     } else if (PyLong_CheckExact(o)) {
         v = o;
         Py_INCREF(v);
     } else {
-        v = PyObject_GetAttrString(o, "cuda_stream");
+        const int is = PyObject_IsInstance(o, g.stream_type);
+        if (is == 0) return false;
+        if (is > 0) v = PyObject_GetAttrString(o, "cuda_stream");
     }
     if (!v) {
         PyErr_Clear();
@@ -102,12 +111,13 @@ PyObject *py_plain(PyObject *, PyObject *args)
     return PyCapsule_New(p, "stepq.plain", free_plain);
 }
 
-// bind(step_ex, load, import, export, dequant, export_pivots, import_pivots, raw_stream)
+// bind(step_ex, load, import, export, dequant, export_pivots, import_pivots, get_device, raw_stream, stream_type)
 PyObject *py_bind(PyObject *, PyObject *args)
 {
-    unsigned long long f[7];
-    PyObject *rs;
-    if (!PyArg_ParseTuple(args, "KKKKKKKO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &rs)) return nullptr;
+    unsigned long long f[8];
+    PyObject *rs, *st;
+    if (!PyArg_ParseTuple(args, "KKKKKKKKOO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &f[7], &rs, &st))
+        return nullptr;
     auto set = [&f](auto &fn, int i) { fn = reinterpret_cast<std::remove_reference_t<decltype(fn)>>(f[i]); };
     set(g.step, 0);
     set(g.load, 1);
@@ -116,8 +126,11 @@ PyObject *py_bind(PyObject *, PyObject *args)
     set(g.dequant, 4);
     set(g.export_pivots, 5);
     set(g.import_pivots, 6);
+    set(g.get_device, 7);
     Py_INCREF(rs);
     Py_XSETREF(g.raw_stream, rs);
+    Py_INCREF(st);
+    Py_XSETREF(g.stream_type, st);
     Py_RETURN_NONE;
 }
 
@@ -153,7 +166,7 @@ PyObject *py_decode(PyObject *, PyObject *const *a, Py_ssize_t n_args)
             !((flags & STEPQ_STEP_KDA_GATE) ? take(a[5], *p, dt, {n, p->Hv, p->dk}, &gate)
                                             : take(a[5], *p, dt, {n, p->Hv}, &gate)) ||
             !take(a[6], *p, dt, {n, p->Hv}, &beta) || !take(a[7], *p, at::kFloat, {n, p->Hv, p->dv}, &o) ||
-            !take_stream(a[8], *p, &s))
+            !take_stream(a[8], &s))
             return -1;
         stepq_status st;
         Py_BEGIN_ALLOW_THREADS;
@@ -178,7 +191,7 @@ PyObject *py_scaled(PyObject *, PyObject *const *a, Py_ssize_t n_args)
         if (!take_ids(a[2], *p, &n, &ids) ||
             !take(a[3], *p, op == kLoad ? at::kFloat : at::kChar, {n, p->Hv, p->dk, p->dv}, &x) ||
             !take(a[4], *p, at::kFloat, {n, p->Hv, p->dk}, &r) || !take(a[5], *p, at::kFloat, {n, p->Hv, p->dv}, &c) ||
-            !take_stream(a[6], *p, &s))
+            !take_stream(a[6], &s))
             return -1;
         const auto *id = static_cast<const int32_t *>(ids);
         const auto m = static_cast<int32_t>(n);
@@ -208,7 +221,7 @@ PyObject *py_tiles(PyObject *, PyObject *const *a, Py_ssize_t n_args)
         const int64_t shape[4] = {n, p->Hv, p->dk, p->dv};
         const bool ok = op == kDequant ? take(a[3], *p, at::kFloat, shape, &x)
                                        : take(a[3], *p, at::kShort, shape, &x) || take(a[3], *p, at::kUInt16, shape, &x);
-        if (!ok || !take_stream(a[4], *p, &s)) return -1;
+        if (!ok || !take_stream(a[4], &s)) return -1;
         const auto *id = static_cast<const int32_t *>(ids);
         const auto m = static_cast<int32_t>(n);
         stepq_status st;
@@ -222,7 +235,7 @@ PyObject *py_tiles(PyObject *, PyObject *const *a, Py_ssize_t n_args)
 }
 
 PyMethodDef methods[] = {
-    {"bind", py_bind, METH_VARARGS, "addresses of the C calls and torch's raw stream query"},
+    {"bind", py_bind, METH_VARARGS, "addresses of the C calls, torch's raw stream query and stream class"},
     {"plain", py_plain, METH_VARARGS, "a pool's handle, device and sizes"},
     {"decode", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(py_decode)), METH_FASTCALL, "one decode step"},
     {"scaled", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(py_scaled)), METH_FASTCALL,

@@ -126,7 +126,8 @@ def native():
         L = lib()
         _stepq_args.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
             "stepq_decode_step_ex", "stepq_pool_load", "stepq_pool_import", "stepq_pool_export", "stepq_pool_dequant",
-            "stepq_pool_export_pivots", "stepq_pool_import_pivots")), torch._C._cuda_getCurrentRawStream)
+            "stepq_pool_export_pivots", "stepq_pool_import_pivots", "hipGetDevice")),
+            torch._C._cuda_getCurrentRawStream, torch.cuda.Stream)
         _native = _stepq_args
     return _native
 

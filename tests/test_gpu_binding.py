@@ -1,6 +1,8 @@
 """The binding's native argument checks: arguments that are not plainly what a
 call takes reach the Python checks (which raise, or take them), streams are
 honoured in every form, and a closed pool is refused."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -84,3 +86,53 @@ def test_closed_pool_is_refused():
         pool.step(**a)
     with pytest.raises(stepq.StepqError):
         pool.dequant(a["slot_ids"], torch.empty((B, H, DK, DV), device=DEV))
+
+
+def test_foreign_stream_objects_are_refused():
+    """Only torch's streams and integers name a stream: an object that merely
+    has an attribute cuda_stream goes through int(), which raises."""
+    class Foreign:
+        cuda_stream = 0
+
+    pool, a = _pool(), _args()
+    before = pool.memory.clone()
+    with pytest.raises(TypeError):
+        pool.step(**a, stream=Foreign())
+    with pytest.raises(TypeError):
+        pool.dequant(a["slot_ids"], torch.empty((B, H, DK, DV), device=DEV), stream=Foreign())
+    assert torch.equal(before, pool.memory)
+
+
+def test_default_stream_is_the_current_devices(monkeypatch):
+    """Without a stream the calls go to torch's current stream, that of the
+    current device, whichever device the pool is on."""
+    pool, a = _pool(), _args()
+    asked = []
+    raw = torch._C._cuda_getCurrentRawStream
+
+    def query(device):
+        asked.append(device)
+        return raw(0)
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, ctypes.POINTER(ctypes.c_int))
+    def other_device(out):
+        out[0] = 5
+        return 0
+
+    class Library:
+        hipGetDevice = other_device
+        __getattr__ = lambda self, name: getattr(real, name)
+
+    real = stepq.lib()
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", query)
+    monkeypatch.setattr(stepq, "_lib", Library())
+    monkeypatch.setattr(stepq, "_native", None)
+    stepq.native()
+    try:
+        args = [a[k] for k in ("slot_ids", "q", "k", "v", "alpha", "beta", "o")]
+        assert stepq._native.decode(pool._plain, *args, None, 0) == 0
+        assert asked == [5]
+    finally:
+        monkeypatch.undo()
+        stepq._native = None
+        stepq.native()
