@@ -1,6 +1,7 @@
-"""The binding's native argument checks: arguments that are not plainly what a
-call takes reach the Python checks (which raise, or take them), streams are
-honoured in every form, and a closed pool is refused."""
+"""The binding's native argument checks: they make every call of plain
+arguments; arguments that are not plainly what a call takes reach the Python
+checks (which raise, or take them), streams are honoured in every form, and a
+closed pool is refused."""
 import ctypes
 
 import numpy as np
@@ -56,9 +57,65 @@ def test_bad_arguments_raise(what):
     assert torch.equal(before, pool.memory)
 
 
-def test_plain_and_other_forms_agree():
-    """Default, integer and object streams, and tensor subclasses (which the
-    native checks leave to the Python ones), give one result."""
+class Subclass(torch.Tensor):
+    """A tensor subclass: the native checks leave it to the Python ones."""
+
+
+def _calls(pool, a, wrap):
+    """(name, what the native module is called with, the public call) of every
+    device call on copies of the same inputs; wrap changes one tensor each."""
+    g = torch.Generator(device=DEV).manual_seed(3)
+    rnd = lambda *s: torch.rand(s, generator=g, device=DEV)
+    gate, o = rnd(B, H, DK), a["o"]
+    ids = a["slot_ids"]
+    act = [a["q"], a["k"], a["v"]]
+    S, r, c = rnd(B, H, DK, DV), rnd(B, H, DK) + 0.5, rnd(B, H, DV) + 0.5
+    codes = torch.zeros((B, H, DK, DV), dtype=torch.int8, device=DEV)
+    piv = torch.zeros((B, H, DK, DV), dtype=torch.int16, device=DEV)
+    out = torch.zeros((B, H, DK, DV), device=DEV)
+    n, P = stepq._native, pool._plain
+    step = lambda flags, gt: (P, wrap(ids), *act, gt, a["beta"], o, None, flags)
+    KDA, REFIT, ABSMAX = stepq.STEPQ_STEP_KDA_GATE, stepq.STEPQ_STEP_REFIT, stepq.STEPQ_STEP_ROW_ABSMAX
+    return [
+        ("load", n.scaled, (0, P, wrap(ids), S, r, c, None), lambda: pool.load(wrap(ids), S, r, c)),
+        ("step", n.decode, step(0, a["alpha"]), lambda: pool.step(wrap(ids), *act, a["alpha"], a["beta"], o)),
+        ("step_kda", n.decode, step(KDA, gate), lambda: pool.step_kda(wrap(ids), *act, gate, a["beta"], o)),
+        ("refit", n.decode, step(REFIT, a["alpha"]),
+         lambda: pool.step(wrap(ids), *act, a["alpha"], a["beta"], o, refit=True)),
+        ("row absmax", n.decode, step(KDA | ABSMAX, gate),
+         lambda: pool.step_kda(wrap(ids), *act, gate, a["beta"], o, refit="row_absmax")),
+        ("export", n.scaled, (2, P, wrap(ids), codes, r, c, None), lambda: pool.export(wrap(ids), codes, r, c)),
+        ("export_pivots", n.tiles, (1, P, wrap(ids), piv, None), lambda: pool.export_pivots(wrap(ids), piv)),
+        ("dequant", n.tiles, (0, P, wrap(ids), out, None), lambda: pool.dequant(wrap(ids), out)),
+        ("import", n.scaled, (1, P, wrap(ids), codes, r, c, None), lambda: pool.import_(wrap(ids), codes, r, c)),
+        ("import_pivots", n.tiles, (2, P, wrap(ids), piv, None), lambda: pool.import_pivots(wrap(ids), piv)),
+    ], (o, codes, r, c, piv, out)
+
+
+def test_native_checks_take_plain_calls_and_leave_the_rest():
+    """Every device call of plain tensors is made by the native module (status
+    0); with a tensor subclass the module makes none (-1), and the Python
+    checks give the same bytes."""
+    results = []
+    for wrap, status in ((lambda t: t, 0), (lambda t: t.as_subclass(Subclass), -1)):
+        pool, a = _pool(), _args()
+        calls, outs = _calls(pool, a, wrap)
+        assert type(wrap(a["slot_ids"])) is (torch.Tensor if status == 0 else Subclass)
+        image = pool.memory.clone()
+        for name, fn, args, public in calls:
+            assert fn(*args) == status, name
+            pool.memory.copy_(image)
+            public()
+            image = pool.memory.clone()
+        torch.cuda.synchronize()
+        results.append([image] + [t.clone() for t in outs])
+    for x, y in zip(*results):
+        assert torch.equal(x, y)
+
+
+def test_stream_forms_agree():
+    """The default, object and integer streams, and a Parameter (a plain tensor
+    to the native checks), give one result."""
     side = torch.cuda.Stream()
     forms = [None, side, side.cuda_stream, "parameter", "with"]
     images = []

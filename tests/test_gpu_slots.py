@@ -1,8 +1,9 @@
 """GPU parity of the bodies for heads of any row-width mix (rows held in pairs
 of row slots), against the fp64 oracle through the C ABI: at each compiled
 pair count the splits that fill it, single rows, class boundaries inside a
-round of slices, empty 4- and 2-bit slots and many FP16 pivot rows, in every
-scale mode."""
+round of slices, empty 4- and 2-bit slots and many FP16 pivot rows, in the two
+scale modes that run these bodies and on both level normalisations.  The frozen
+mode checks the generic body on the same shapes."""
 import numpy as np
 import pytest
 import torch
@@ -31,21 +32,29 @@ def _bits(rng, dk, heads):
     return np.stack([rng.permutation(np.repeat(np.array([8, 4, 2, 16], np.uint8), h)) for h in heads])
 
 
+def lv_step(bits, levels):
+    """The level step nu of each row: a code q stands for r c nu q."""
+    b = bits.astype(np.float64)
+    return 2.0 ** (8 - b) if levels == stepq.STEPQ_LEVELS_POW2 else 1.0 / (2.0 ** (b - 1) - 1)
+
+
+@pytest.mark.parametrize("levels", [stepq.STEPQ_LEVELS_ABSMAX, stepq.STEPQ_LEVELS_POW2])
 @pytest.mark.parametrize("mode", [False, True, "row_absmax"])
 @pytest.mark.parametrize("act,kda", [("f32", False), ("bf16", True)])
 @pytest.mark.parametrize("shape", list(SHAPES))
-def test_slot_bodies_one_step(shape, act, kda, mode):
+def test_slot_bodies_one_step(shape, act, kda, mode, levels):
     dk, dv, heads = SHAPES[shape]
-    print(f"slot bodies {shape} act={act} kda={kda} mode={mode}", flush=True)
-    rng = np.random.default_rng(len(shape) * 1000 + dk)
+    lv = dict(levels=levels)
+    print(f"slot bodies {shape} act={act} kda={kda} mode={mode} levels={levels}", flush=True)
+    rng = np.random.default_rng(len(shape) * 1000 + dk + 7 * levels)
     bits = _bits(rng, dk, heads)
     Hv, n_slots, B = len(heads), 3, 2
     S = (rng.standard_normal((n_slots, Hv, dk, dv)) * 0.05).astype(np.float32)
     tb = np.broadcast_to(bits[None], (n_slots,) + bits.shape).reshape(-1, dk)
-    r, c = oracle.fit_absmax(S.reshape(-1, dk, dv), bits=tb)
+    r, c = oracle.fit_absmax(S.reshape(-1, dk, dv), bits=tb, **lv)
     c = np.where(c > 0, c, 1.0)
-    codes, pv = oracle.quantize(S.reshape(-1, dk, dv).astype(np.float64), r, c, tb)
-    pool = stepq.Pool(n_slots, Hv, Hv, dk, dv, bits, device=DEV)
+    codes, pv = oracle.quantize(S.reshape(-1, dk, dv).astype(np.float64), r, c, tb, **lv)
+    pool = stepq.Pool(n_slots, Hv, Hv, dk, dv, bits, device=DEV, levels=levels)
     all_ids = torch.arange(n_slots, dtype=torch.int32, device=DEV)
     up = lambda a, *s: torch.from_numpy(np.ascontiguousarray(a.reshape(*s))).to(DEV)
     pool.import_(all_ids, up(codes, n_slots, Hv, dk, dv), up(r.astype(np.float32), n_slots, Hv, dk),
@@ -80,15 +89,25 @@ def test_slot_bodies_one_step(shape, act, kda, mode):
     if mode is True:
         wt = np.broadcast_to(wrow[None].astype(np.float64), (B, Hv, dk)).reshape(-1, dk)
         new, rn, cn, o_ref, ex, npv = oracle.decode_step_refit(*args, w=wt, want=("y", "c_range"),
-                                                               tie_window=PT.TIE_WINDOW, pv=pv[tiles])
-        PT.compare_refit(got[tiles], gr[tiles], gc[tiles], new, rn, cn, ex["y"], ex["c_range"], tb[tiles], shape)
+                                                               tie_window=PT.TIE_WINDOW, pv=pv[tiles], **lv)
+        lo, hi = ex["c_range"]
+        if dk == 1:
+            # one row: c' = |X| / (r' q_b), and X = d S + beta k (v - d S k) may cancel.  Its fp32 error is at most
+            # 4 roundings of the summed magnitudes, so c' may lie that far from the range, relative to |X|
+            S0 = codes[tiles][:, 0] * (r[tiles] * c[tiles]) * lv_step(tb[tiles], levels)
+            kk, vv, d, b = args[5], args[6], args[7].reshape(-1, 1), args[8][:, None]
+            X = d * S0 + b * kk * (vv - d * S0 * kk)
+            size = np.abs(d * S0) + np.abs(b * kk) * (np.abs(vv) + np.abs(d * S0 * kk))
+            e = 4 * 2.0 ** -24 * size / np.maximum(np.abs(X), 1e-300)
+            lo, hi = lo * np.maximum(1 - e, 0.0), hi * (1 + e)
+        PT.compare_refit(got[tiles], gr[tiles], gc[tiles], new, rn, cn, ex["y"], (lo, hi), tb[tiles], shape)
         y = ex["y"]
     elif mode == "row_absmax":
-        new, rn, cn, o_ref, y, npv = oracle.decode_step_rowmax(*args, want_y=True, pv=pv[tiles])
+        new, rn, cn, o_ref, y, npv = oracle.decode_step_rowmax(*args, want_y=True, pv=pv[tiles], **lv)
         ones = np.ones(cn.shape)
         PT.compare_refit(got[tiles], gr[tiles], gc[tiles], new, rn, cn, y, (ones, ones), tb[tiles], shape)
     else:
-        new, o_ref, y, npv = oracle.decode_step(*args, want_y=True, pv=pv[tiles])
+        new, o_ref, y, npv = oracle.decode_step(*args, want_y=True, pv=pv[tiles], **lv)
         PT.compare_codes(got[tiles], new, y, shape)
         assert np.array_equal(gr[tiles], r[tiles]) and np.array_equal(gc[tiles], c[tiles])
     PT.compare_pivots(gpv[tiles], npv, y, tb[tiles] == 16, shape)
@@ -138,3 +157,57 @@ def test_row_absmax_of_rowmix_heads_in_fp32(kda):
         out.append([x[:, :H].clone() for x in (o, codes, gr, gc, piv)])
     for name, a, b in zip(("o", "codes", "r", "c", "pivots"), *out):
         assert torch.equal(a, b), (name, int((a != b).sum()))
+
+
+@pytest.mark.parametrize("mode", [True, "row_absmax"])
+@pytest.mark.parametrize("shape", ["dv64-6pairs", "dv128-6pairs", "dv128-12pairs", "rowmix"])
+def test_infinite_and_nan_values_stay_in_their_tile(shape, mode):
+    """Infinite and NaN values of v, k, q or a gate make their own tile's o
+    non-finite where they enter it, and change no bit of any other tile, in the
+    bodies that give slots without a row zero constants."""
+    dk, dv, heads = SHAPES.get(shape, (128, 128, [(64, 60, 0, 4), (33, 95, 0, 0), (1, 127, 0, 0), (119, 1, 0, 8)]))
+    rng = np.random.default_rng(31)
+    bits = _bits(rng, dk, heads)
+    Hv, B = len(heads), 6
+    S = (rng.standard_normal((B, Hv, dk, dv)) * 0.05).astype(np.float32)
+    r = np.sqrt(np.abs(S).mean(-1)).astype(np.float32)
+    c = np.full((B, Hv, dv), 0.3, np.float32)
+    q, k = (rng.standard_normal((B, Hv, dk)).astype(np.float32) * dk ** -0.5 for _ in range(2))
+    v = rng.standard_normal((B, Hv, dv)).astype(np.float32)
+    gate, be = rng.uniform(0.5, 1, (B, Hv)).astype(np.float32), rng.uniform(0.2, 1, (B, Hv)).astype(np.float32)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    ids = torch.arange(B, dtype=torch.int32, device=DEV)
+
+    def run(x):
+        pool = stepq.Pool(B, Hv, Hv, dk, dv, bits, device=DEV)
+        pool.memory.zero_()
+        pool.load(ids, up(S), up(r), up(c))
+        o = torch.empty((B, Hv, dv), device=DEV)
+        pool.step(ids, *(up(t) for t in x), o, refit=mode)
+        g = (torch.empty((B, Hv, dk, dv), dtype=torch.int8, device=DEV), torch.empty((B, Hv, dk), device=DEV),
+             torch.empty((B, Hv, dv), device=DEV))
+        piv = torch.empty((B, Hv, dk, dv), dtype=torch.int16, device=DEV)
+        pool.export(ids, *g)
+        pool.export_pivots(ids, piv)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (o, *g, piv)]
+
+    clean = run((q, k, v, gate, be))
+    assert np.isfinite(clean[0]).all()
+    v2, k2, q2, gate2 = v.copy(), k.copy(), q.copy(), gate.copy()
+    v2[1, 0, 3], v2[1, 1, 5], k2[2, 0, 0], q2[3, 1, dk - 1], gate2[4, 0] = np.inf, np.nan, np.inf, np.nan, np.nan
+    hit = {(1, 0), (1, 1), (2, 0), (3, 1), (4, 0)}
+    got = run((q2, k2, v2, gate2, be))
+    for b in range(B):
+        for h in range(Hv):
+            if (b, h) in hit:
+                assert not np.isfinite(got[0][b, h]).all(), (b, h)
+            else:
+                for x, y in zip(clean, got):
+                    assert np.array_equal(x[b, h], y[b, h]), (b, h)
+    # v enters column by column: o of the others is untouched
+    assert np.array_equal(np.isfinite(got[0][1, 0]), np.arange(dv) != 3)
+    assert np.array_equal(got[0][1, 0][np.arange(dv) != 3], clean[0][1, 0][np.arange(dv) != 3])
+    # q reaches o only: the new state is that of the clean step
+    for x, y in zip(clean[1:], got[1:]):
+        assert np.array_equal(x[3, 1], y[3, 1])
