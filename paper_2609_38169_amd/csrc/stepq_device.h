@@ -83,27 +83,19 @@ __device__ __forceinline__ int xcd_tile(int wg, int n)
 
 struct GroupRows {
     int bits;   // width of the group's rows
-    int nslot;  // rows per group (8 / bits)
-    int p0;     // physical row of slot 0
-    int pend;   // one past the last physical row of this width
     int x0;     // row-table index of slot 0
 };
 
 // Physical rows: the n16 pivot rows first, then the integer rows 8, 4, 2;
 // the row table and the groups cover the integer rows only.  A width class
 // may hold more groups than its rows fill (g8 > n8, or a padded 4- or 2-bit
-// class): its slots past the class's last row are empty (p0 + s >= pend)
-// and their codes stay 0.
+// class): its slots past the class's last row are empty (slot_row) and their
+// codes stay 0.
 __device__ __forceinline__ GroupRows group_rows(const HeadInfo &hi, int g)
 {
-    const int P = hi.n16;
-    if (g < hi.g8) return {8, 1, P + g, P + hi.n8, g};
-    if (g < hi.g8 + hi.g4) {
-        const int k = g - hi.g8;
-        return {4, 2, P + hi.n8 + 2 * k, P + hi.n8 + hi.n4, hi.g8 + 2 * k};
-    }
-    const int k = g - hi.g8 - hi.g4;
-    return {2, 4, P + hi.n8 + hi.n4 + 4 * k, P + hi.n8 + hi.n4 + hi.n2, hi.g8 + 2 * hi.g4 + 4 * k};
+    if (g < hi.g8) return {8, g};
+    if (g < hi.g8 + hi.g4) return {4, hi.g8 + 2 * (g - hi.g8)};
+    return {2, hi.g8 + 2 * hi.g4 + 4 * (g - hi.g8 - hi.g4)};
 }
 
 // Row-table slot x -> physical row (or -1 for an empty slot) and its width.
@@ -1021,46 +1013,9 @@ __device__ __forceinline__ f32x4 mfma_view(const _Float16 (&A)[4][4], const uint
     return mfma4x4x4(a, b0, b1, d);
 }
 
-// Column E of the row-mix thread's two sums: one chain over the word groups
-// and their slot views (one accumulator live), written to LDS unscaled.
-// The slot-0 views of the group holding the width boundary (vb) come in
-// formed; the other views are formed again for each column rather than kept.
-template <int E, class W>
-__device__ __forceinline__ void rowmix_column(const DecodeShared<128> &sh, const W &w,
-                                              const uint32_t (&vb)[4], int slice, int cg, int g8, int ng, int ek,
-                                              int eq, float *redK, float *redQ)
-{
-    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (32 * j >= ng) break;
-        if (32 * j + 32 <= g8) {
-            // 8-bit words only: their bytes are the codes
-            const uint32_t v[4] = {w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
-            d = mfma_view<E>(sh.aopv[slice][j][0], v, cg, d);
-        } else {
-            uint32_t v[4];
-            if (32 * j >= g8) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) v[k] = slot_top<4>(w[4 * j + k], 0);
-                d = mfma_view<E>(sh.aopv[slice][j][0], v, cg, d);
-            } else {
-                d = mfma_view<E>(sh.aopv[slice][j][0], vb, cg, d);    // the group of the width boundary
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = slot_top<4>(w[4 * j + k], 1);
-            d = mfma_view<E>(sh.aopv[slice][j][1], v, cg, d);
-        }
-    }
-    redK[E] = __builtin_amdgcn_ldexpf(d[0] + d[1], -ek);
-    redQ[E] = __builtin_amdgcn_ldexpf(d[2] + d[3], -eq);
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 // All four columns of the row-mix thread's two sums in one pass over the
 // word groups (four accumulators live): each group's slot views are formed
-// once rather than once per column.  For bodies whose register peak lies
-// after the column phase (the refitting body).
+// once rather than once per column.
 template <class W>
 __device__ __forceinline__ void rowmix_columns4(const DecodeShared<128> &sh, const W &w, int slice,
                                                 int cg, int g8, int ng, int ek, int eq, float *redK, float *redQ)
@@ -1106,15 +1061,13 @@ __device__ __forceinline__ void rowmix_columns4(const DecodeShared<128> &sh, con
     redQ[3] = __builtin_amdgcn_ldexpf(d3[2] + d3[3], -eq);
 }
 
-// The first half of the row-mix bodies (decode_rowmix and the refitting
-// body's refit_rowmix): row constants (divided by the widths' clamp scales
+// The first half of the row-mix bodies (decode_rowmix, and refit_slots for
+// the fit of row-mix heads): row constants (divided by the widths' clamp scales
 // when SCALED, the form the frozen-scale requantization works in), both sums
 // over rows on the matrix cores, the pivot rows' share, and the column
 // phase: o is written and delta_j / c_j is left in sh.bcol.  w: the
 // thread's 16 code words (0 past the head's last group); pr: its pivot row.
-// ALLCOLS: the four columns in one pass (rowmix_columns4), else one at a
-// time (fewer registers).
-template <bool DIAG, bool SCALED, bool ALLCOLS = false, class W, class F, class Ops>
+template <bool DIAG, bool SCALED, class W, class F, class Ops>
 __device__ __forceinline__ void rowmix_sums(const DecodeArgs &a, const TileCtx &t, DecodeShared<128> &sh,
                                             const W &w, const PivotRegs<128, kCompactPivots> &pr,
                                             const Ops &op, const LevelTable &lv, int g8, int ng,
@@ -1131,24 +1084,7 @@ __device__ __forceinline__ void rowmix_sums(const DecodeArgs &a, const TileCtx &
     row_operands_rowmix(t.hi, sh, ek, eq);
 
     float *redK = &sh.red[0][slice][cg].x, *redQ = &sh.red[1][slice][cg].x;
-    // slot-0 views of the word group holding the width boundary (if any),
-    // formed once: there the width changes from one slice to the next
-    if constexpr (ALLCOLS) {
-        rowmix_columns4(sh, w, slice, cg, g8, ng, ek, eq, redK, redQ);
-    } else {
-        uint32_t vb[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if ((g8 >> 5) == j && (g8 & 31) != 0) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    vb[k] = slice + 8 * (4 * j + k) < g8 ? w[4 * j + k] : slot_top<4>(w[4 * j + k], 0);
-            }
-        rowmix_column<0>(sh, w, vb, slice, cg, g8, ng, ek, eq, redK, redQ);
-        rowmix_column<1>(sh, w, vb, slice, cg, g8, ng, ek, eq, redK, redQ);
-        rowmix_column<2>(sh, w, vb, slice, cg, g8, ng, ek, eq, redK, redQ);
-        rowmix_column<3>(sh, w, vb, slice, cg, g8, ng, ek, eq, redK, redQ);
-    }
+    rowmix_columns4(sh, w, slice, cg, g8, ng, ek, eq, redK, redQ);
     pivot_partials_slice(t, slice, cg, pr, sh);
 
     column_sums<128>(a, t.tile, DIAG ? 1.0f : t.alpha, t.beta, sh, kappa, sh.cpiv[tid & 127], sh.bcol[tid & 127]);

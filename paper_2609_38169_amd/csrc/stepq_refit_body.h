@@ -62,14 +62,10 @@ struct RefitShared {
 
 // One row partial of a thread (4 columns of one row slot), combined with
 // that of the neighbouring lane (the next 4 columns of the same row) before
-// it goes to LDS: sums for the dual-axis fit, maxima (of non-negative
-// values) for the row absmax.  Both lanes of a pair write the same value.
-template <int DV, Refit MODE>
-__device__ __forceinline__ void put_row_partial(RefitShared<DV> &sh, int x, int cg, float acc)
+// it goes to LDS.  Both lanes of a pair write the same value.
+__device__ __forceinline__ void put_row_partial(RefitShared<128> &sh, int x, int cg, float acc)
 {
-    if constexpr (MODE == Refit::DualAxis) acc += dpp_term<0xB1, 0xF>(acc);    // quad_perm [1,0,3,2]
-    else acc = __uint_as_float(max(__float_as_uint(acc), dpp_bits<0xB1, 0xF>(__float_as_uint(acc))));
-    sh.u.rowp[x][cg >> 1] = acc;
+    sh.u.rowp[x][cg >> 1] = acc + dpp_term<0xB1, 0xF>(acc);    // quad_perm [1,0,3,2]
 }
 
 // Row partial over the thread's 4 columns: sum_e c_e |y_e| (dual axis) or
@@ -176,7 +172,7 @@ __device__ __forceinline__ void refit_colfit(SH &sh, int j, float *cc_out)
 // y of a word from the row-pair registers of the matrix-core path; the row
 // partial sum_e c_e |y| (or max) of each slot goes to LDS.  Slot s of the
 // word is thread row r0 + s (a constant once the caller's loops unroll).
-template <int B, bool DIAG, Refit MODE>
+template <int B, bool DIAG>
 __device__ __forceinline__ void word_y_p(const uint32_t (&Ub)[4][4][2], int r0, RefitShared<128> &sh, int x0, int cg,
                                          float al_w, const float (&bc)[4], const float (&cc)[4], float *Y)
 {
@@ -197,7 +193,7 @@ __device__ __forceinline__ void word_y_p(const uint32_t (&Ub)[4][4][2], int r0, 
             y[2] = fma_mix<0>(al, Ub[2][g][h], a_s * bc[2]);
             y[3] = fma_mix<0>(al, Ub[3][g][h], a_s * bc[3]);
         }
-        put_row_partial<128, MODE>(sh, x0 + s, cg, row_partial<MODE>(y, cc));
+        put_row_partial(sh, x0 + s, cg, row_partial<Refit::DualAxis>(y, cc));
     }
 }
 
@@ -206,7 +202,7 @@ __device__ __forceinline__ void word_y_p(const uint32_t (&Ub)[4][4][2], int r0, 
 // diagonal 4x4x4 block gives y = al U + (av_i bc_j) for the group's 4 rows
 // (within one ulp of word_y_p's FMA); Y[4 r + e] for thread row r, and the
 // row partials to LDS.
-template <int M8, int M4, int M2, Refit MODE>
+template <int M8, int M4, int M2>
 __device__ __forceinline__ void refit_y_mfma(const uint32_t (&Ub)[4][4][2], RefitShared<128> &sh, int tid, int slice,
                                              int cg, float alpha, const float (&bc)[4], const float (&cc)[4],
                                              float (&Y)[64])
@@ -228,8 +224,8 @@ __device__ __forceinline__ void refit_y_mfma(const uint32_t (&Ub)[4][4][2], Refi
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            put_row_partial<128, MODE>(sh, thread_row_slot<M8, M4>(4 * g + k, slice), cg,
-                                 row_partial<MODE>(&Y[4 * (4 * g + k)], cc));
+            put_row_partial(sh, thread_row_slot<M8, M4>(4 * g + k, slice), cg,
+                            row_partial<Refit::DualAxis>(&Y[4 * (4 * g + k)], cc));
     }
 }
 
@@ -309,11 +305,10 @@ __device__ __forceinline__ void ld4(const float *p, float (&v)[4])
 // updated in binary16, and take no part in the fits; the padded mix's empty
 // slots (zero codes, no row) get h = W = 0, so they add nothing to the fits
 // and keep zero codes.
-template <bool BF16, bool DIAG, int M8, int M4, int M2, Refit MODE, bool PIV = false>
+template <bool BF16, bool DIAG, int M8, int M4, int M2, bool PIV = false>
 __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx &t, RefitShared<128> &sh)
 {
     // uniform layouts take the lean row-absmax body of stepq_rowmax.hip
-    static_assert(MODE == Refit::DualAxis, "the uniform refitting body runs the dual-axis fit");
     constexpr int M = M8 + M4 + M2;
     constexpr int NE = 4 * (M8 + 2 * M4 + 4 * M2);
     constexpr int X4 = 8 * M8, X2 = 8 * M8 + 16 * M4;
@@ -357,21 +352,21 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
     bool y_done = false;
     if constexpr (!DIAG) {
         if (gate_on_matrix_cores<M8, M4, M2>(t.alpha)) {
-            refit_y_mfma<M8, M4, M2, MODE>(Ub, sh, tid, slice, cg, t.alpha, bc, cc, Y);
+            refit_y_mfma<M8, M4, M2>(Ub, sh, tid, slice, cg, t.alpha, bc, cc, Y);
             y_done = true;
         }
     }
     if (!y_done) {
 #pragma unroll
         for (int m = 0; m < M8; ++m)
-            word_y_p<8, DIAG, MODE>(Ub, m, sh, slice + 8 * m, cg, t.alpha, bc, cc, &Y[4 * m]);
+            word_y_p<8, DIAG>(Ub, m, sh, slice + 8 * m, cg, t.alpha, bc, cc, &Y[4 * m]);
 #pragma unroll
         for (int m = 0; m < M4; ++m)
-            word_y_p<4, DIAG, MODE>(Ub, M8 + 2 * m, sh, X4 + 2 * (slice + 8 * m), cg, t.alpha * (1.0f / 16.0f), bc,
+            word_y_p<4, DIAG>(Ub, M8 + 2 * m, sh, X4 + 2 * (slice + 8 * m), cg, t.alpha * (1.0f / 16.0f), bc,
                                     cc, &Y[Y4 + 8 * m]);
 #pragma unroll
         for (int m = 0; m < M2; ++m)
-            word_y_p<2, DIAG, MODE>(Ub, M8 + 2 * M4 + 4 * m, sh, X2 + 4 * (slice + 8 * m), cg,
+            word_y_p<2, DIAG>(Ub, M8 + 2 * M4 + 4 * m, sh, X2 + 4 * (slice + 8 * m), cg,
                                     t.alpha * (1.0f / 64.0f), bc, cc, &Y[Y2 + 16 * m]);
     }
     __syncthreads();
@@ -381,14 +376,14 @@ __device__ __forceinline__ void refit_uniform(const DecodeArgs &a, const TileCtx
             int bw;
             const int p = slot_row(t.hi, tid, bw);
             if (p >= 0) {
-                rr_out[p] = refit_row<MODE, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]), bw, sh.d.sr[p],
+                rr_out[p] = refit_row<Refit::DualAxis, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]), bw, sh.d.sr[p],
                                                 sh.wphys[p], lv, sh.hrow[tid], sh.wrow[tid]);
             } else {
                 sh.hrow[tid] = 0.f;
                 sh.wrow[tid] = 0.f;
             }
         } else {
-            rr_out[tid] = refit_row<MODE, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]),
+            rr_out[tid] = refit_row<Refit::DualAxis, 16>(reinterpret_cast<const float4 *>(&sh.u.rowp[tid][0]),
                                               tid < X4 ? 8 : (tid < X2 ? 4 : 2), op.r, sh.wphys[tid], lv,
                                               sh.hrow[tid], sh.wrow[tid]);
         }
@@ -580,7 +575,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
     // rounding boundary depends on their last bits.
     float Y[NP][8];
     if constexpr (ROWMIX) {
-        rowmix_sums<DIAG, false, true>(a, t, sh.d, w16, pr, op, lv, g.g8, ng, [&] {
+        rowmix_sums<DIAG, false>(a, t, sh.d, w16, pr, op, lv, g.g8, ng, [&] {
             if (row.slice >= 0) {
                 // row-table slot of physical row tid: the integer rows in order
                 const int x = tid - static_cast<int>(t.hi.n16);
@@ -756,7 +751,7 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
 }
 
 // A tile of uniform layout L: codes (1024 bytes per word-step), then r, c.
-template <bool BF16, bool DIAG, int L, Refit MODE>
+template <bool BF16, bool DIAG, int L>
 __device__ __forceinline__ void run_refit_uniform(const DecodeArgs &a, TileCtx &t, int slot, RefitShared<128> &sh)
 {
     constexpr UniformLayout u = kUniformLayouts[L - 1];
@@ -765,17 +760,17 @@ __device__ __forceinline__ void run_refit_uniform(const DecodeArgs &a, TileCtx &
     t.codes = reinterpret_cast<uint32_t *>(rec);
     t.rr = reinterpret_cast<const float *>(rec + r_off);
     t.cc = t.rr + 128;
-    refit_uniform<BF16, DIAG, u.m8, u.m4, u.m2, MODE>(a, t, sh);
+    refit_uniform<BF16, DIAG, u.m8, u.m4, u.m2>(a, t, sh);
 }
 
 // A padded pivot head of uniform layout L (its row counts from the head
 // list), or a layout-L head taken as one with no pivot rows.
-template <bool BF16, bool DIAG, int L, Refit MODE>
+template <bool BF16, bool DIAG, int L>
 __device__ __forceinline__ void run_refit_uniform_piv(const DecodeArgs &a, TileCtx &t, int slot, RefitShared<128> &sh)
 {
     constexpr UniformLayout u = kUniformLayouts[L - 1];
     padded_pivot_tile<L>(a, t, slot);
-    refit_uniform<BF16, DIAG, u.m8, u.m4, u.m2, MODE, true>(a, t, sh);
+    refit_uniform<BF16, DIAG, u.m8, u.m4, u.m2, true>(a, t, sh);
 }
 
 // NP: the row pairs of the slot bodies (layouts 0 and kRowMix; 0 for the
@@ -807,23 +802,23 @@ __global__ __launch_bounds__(256, refit_waves(NP)) void refit_kernel(DecodeArgs 
     t.alpha = DIAG ? 1.0f : act_ld<BF16>(a.alpha, t.tile);
     t.beta = act_ld<BF16>(a.beta, t.tile);
     if constexpr (UNIFORM) {
-        run_refit_uniform<BF16, DIAG, LAYOUT, MODE>(a, t, slot, sh);
+        run_refit_uniform<BF16, DIAG, LAYOUT>(a, t, slot, sh);
     } else if constexpr (DV == 128 && LAYOUT > kPivotUniformBase && LAYOUT <= kPivotUniformBase + kNumUniformLayouts) {
-        run_refit_uniform_piv<BF16, DIAG, LAYOUT - kPivotUniformBase, MODE>(a, t, slot, sh);
+        run_refit_uniform_piv<BF16, DIAG, LAYOUT - kPivotUniformBase>(a, t, slot, sh);
     } else if constexpr (DV == 128 && LAYOUT > kMixedPivotBase && LAYOUT <= kMixedPivotBase + 2) {
         // layout-L heads and layout-L padded pivot heads in one launch of one
         // body: a layout-L head is a padded pivot head with no pivot rows
-        run_refit_uniform_piv<BF16, DIAG, LAYOUT - kMixedPivotBase, MODE>(a, t, slot, sh);
+        run_refit_uniform_piv<BF16, DIAG, LAYOUT - kMixedPivotBase>(a, t, slot, sh);
     } else if constexpr (DV == 128 && LAYOUT == kMultiUniform) {
         // heads of several uniform layouts and whole FP16 heads in one launch
         // (the head list), each tile on its own body; a whole FP16 head has
         // no integer rows to fit and takes the frozen-step body
         switch (t.layout) {
-        case 1: run_refit_uniform<BF16, DIAG, 1, MODE>(a, t, slot, sh); break;
-        case 2: run_refit_uniform<BF16, DIAG, 2, MODE>(a, t, slot, sh); break;
-        case 3: run_refit_uniform<BF16, DIAG, 3, MODE>(a, t, slot, sh); break;
-        case 4: run_refit_uniform<BF16, DIAG, 4, MODE>(a, t, slot, sh); break;
-        case 5: run_refit_uniform<BF16, DIAG, 5, MODE>(a, t, slot, sh); break;
+        case 1: run_refit_uniform<BF16, DIAG, 1>(a, t, slot, sh); break;
+        case 2: run_refit_uniform<BF16, DIAG, 2>(a, t, slot, sh); break;
+        case 3: run_refit_uniform<BF16, DIAG, 3>(a, t, slot, sh); break;
+        case 4: run_refit_uniform<BF16, DIAG, 4>(a, t, slot, sh); break;
+        case 5: run_refit_uniform<BF16, DIAG, 5>(a, t, slot, sh); break;
         default: run_f16head<BF16, DIAG>(a, t, slot, sh.d); break;
         }
     } else {

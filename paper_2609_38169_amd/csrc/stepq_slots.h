@@ -1,5 +1,7 @@
-// The decode bodies for heads of any row-width mix ("slot" bodies): any d_k,
-// d_v = 64 or 128, FP16 pivot rows, the row splits of a row-unit calibration.
+// The refit and row-absmax bodies for heads of any row-width mix ("slot"
+// bodies, completed in stepq_refit_body.h): any d_k, d_v = 64 or 128, FP16
+// pivot rows, the row splits of a row-unit calibration.  Frozen steps of these
+// heads run the generic or the row-mix body (stepq_kernels.hip).
 //
 // Every thread holds 4 columns (word cg of a row group) of its slice's rows,
 // in NP pairs of row slots.  The classes take whole pairs: the 8-bit words of
