@@ -756,8 +756,9 @@ __device__ __forceinline__ float row_constants_mfma_piv(const HeadInfo &hi, floa
 
 // Column sums of the per-thread partials, residual, readout, column factor
 // of the code-space update.  cj, vj: the scale and value of the column the
-// thread owns (own_column).  Ends with a barrier.
-template <int DV, bool TOGETHER = false, class SH>
+// thread owns (own_column).  TREE: the slices' partials are added in pairs.
+// Ends with a barrier.
+template <int DV, bool TOGETHER = false, bool TREE = false, class SH>
 __device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta, SH &sh,
                                             float kappa, float cj, float vj);
 
@@ -774,7 +775,7 @@ __device__ __forceinline__ void column_phase(const DecodeArgs &a, int tile, floa
 }
 
 // The column phase once every thread has written its partials to sh.red.
-template <int DV, bool TOGETHER, class SH>
+template <int DV, bool TOGETHER, bool TREE, class SH>
 __device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float alpha, float beta, SH &sh,
                                             float kappa, float cj, float vj)
 {
@@ -783,11 +784,31 @@ __device__ __forceinline__ void column_sums(const DecodeArgs &a, int tile, float
     if (const int j = own_column<DV, TOGETHER>(); j >= 0) {
         const float *rk = reinterpret_cast<const float *>(&sh.red[0][0][0]);
         const float *rq = reinterpret_cast<const float *>(&sh.red[1][0][0]);
-        float sk = rk[j], sq = rq[j];
+        float sk, sq;
+        if constexpr (TREE) {
+            float pk[NSL], pq[NSL];
 #pragma unroll
-        for (int s = 1; s < NSL; ++s) {
-            sk += rk[s * DV + j];
-            sq += rq[s * DV + j];
+            for (int s = 0; s < NSL; ++s) {
+                pk[s] = rk[s * DV + j];
+                pq[s] = rq[s * DV + j];
+            }
+#pragma unroll
+            for (int w = 1; w < NSL; w *= 2)
+#pragma unroll
+                for (int s = 0; s < NSL; s += 2 * w) {
+                    pk[s] += pk[s + w];
+                    pq[s] += pq[s + w];
+                }
+            sk = pk[0];
+            sq = pq[0];
+        } else {
+            sk = rk[j];
+            sq = rq[j];
+#pragma unroll
+            for (int s = 1; s < NSL; ++s) {
+                sk += rk[s * DV + j];
+                sq += rq[s * DV + j];
+            }
         }
         const float delta = vj - alpha * (cj * sk);     // v - alpha (S^T k)
         a.o[static_cast<size_t>(tile) * DV + j] = alpha * (cj * sq) + beta * kappa * delta;

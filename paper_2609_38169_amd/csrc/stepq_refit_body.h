@@ -606,23 +606,42 @@ __device__ __forceinline__ void refit_slots(const DecodeArgs &a, const TileCtx &
         const float alpha = uniform_f(t.alpha), beta = uniform_f(t.beta);
         const float kappa = slot_constants<DIAG>(t.hi, dk, alpha, beta, op, sh.d, lv, row);
         slot_fields<NP, HAS2>(g, live, wa, wb, Y);
+        // row-mix heads: two chains a column and the slices in pairs: o's error
+        // against 64 bits (64 requests x 16 heads, channel-wise gates, fp32) is
+        // 9.0e-8, as with the matrix cores' fewer roundings; 9.7e-8 in one chain
+        constexpr bool kTwoChains = !HAS2;
         float acK[4] = {0.f, 0.f, 0.f, 0.f}, acQ[4] = {0.f, 0.f, 0.f, 0.f};
+        float acK1[4] = {0.f, 0.f, 0.f, 0.f}, acQ1[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             if (!(live >> p & 1u)) continue;
             const float4 c = *reinterpret_cast<const float4 *>(&sh.d.kq[slice][2 * p]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                acK[e] = fmaf(c.z, Y[p][4 + e], fmaf(c.x, Y[p][e], acK[e]));
-                acQ[e] = fmaf(c.w, Y[p][4 + e], fmaf(c.y, Y[p][e], acQ[e]));
+                if constexpr (kTwoChains) {
+                    acK[e] = fmaf(c.x, Y[p][e], acK[e]);
+                    acQ[e] = fmaf(c.y, Y[p][e], acQ[e]);
+                    acK1[e] = fmaf(c.z, Y[p][4 + e], acK1[e]);
+                    acQ1[e] = fmaf(c.w, Y[p][4 + e], acQ1[e]);
+                } else {
+                    acK[e] = fmaf(c.z, Y[p][4 + e], fmaf(c.x, Y[p][e], acK[e]));
+                    acQ[e] = fmaf(c.w, Y[p][4 + e], fmaf(c.y, Y[p][e], acQ[e]));
+                }
             }
             if constexpr (kInOrder) __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (kTwoChains) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acK[e] += acK1[e];
+                acQ[e] += acQ1[e];
+            }
         }
         pivot_acc(t, slice, cg, pr, sh.d, acK, acQ);
         sh.d.red[0][slice][cg] = make_float4(acK[0], acK[1], acK[2], acK[3]);
         sh.d.red[1][slice][cg] = make_float4(acQ[0], acQ[1], acQ[2], acQ[3]);
-        column_sums<DV>(a, t.tile, DIAG ? 1.0f : alpha, beta, sh.d, kappa, sh.d.cpiv[tid & (DV - 1)],
-                        sh.d.bcol[tid & (DV - 1)]);
+        column_sums<DV, false, kTwoChains>(a, t.tile, DIAG ? 1.0f : alpha, beta, sh.d, kappa,
+                                           sh.d.cpiv[tid & (DV - 1)], sh.d.bcol[tid & (DV - 1)]);
     }
 
     // pass 1: y on the old scales and the row partials
