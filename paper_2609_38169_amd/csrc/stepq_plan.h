@@ -23,8 +23,8 @@ namespace stepq {
 //    by class, larger classes first.  Class c is order[cls_off[c] ..
 //    cls_off[c] + cls_cnt[c]) and launches the body cls_code[c]; when
 //    mixed_code is not 0, a frozen decode step is one launch of that body
-//    over the whole of order instead (the refitting steps always launch per
-//    class).
+//    over the whole of order instead, and so is a refit where refit_combined
+//    says so (the other refitting steps launch per class).
 struct LaunchPlan {
     int layout = 0;
     std::vector<LaunchHead> order;
