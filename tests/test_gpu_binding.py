@@ -113,6 +113,30 @@ def test_native_checks_take_plain_calls_and_leave_the_rest():
         assert torch.equal(x, y)
 
 
+def test_checks_in_python_where_the_module_is_not_built(monkeypatch):
+    """A pool of a package built without the module says so once and gives the
+    same bytes through the Python checks."""
+    results = []
+    for built in (True, False):
+        if not built:
+            monkeypatch.setattr(stepq, "_native", None)
+            exists = stepq.os.path.exists
+            monkeypatch.setattr(stepq.os.path, "exists", lambda p: not str(p).endswith("_stepq_args.so") and exists(p))
+            with pytest.warns(UserWarning, match="_stepq_args"):
+                pool = _pool()
+        else:
+            pool = _pool()
+        a = _args()
+        calls, outs = _calls(pool, a, lambda t: t)
+        for name, fn, args, public in calls:
+            assert built or fn(*args) == -1, name
+            public()
+        torch.cuda.synchronize()
+        results.append([pool.memory.clone()] + [t.clone() for t in outs])
+    for x, y in zip(*results):
+        assert torch.equal(x, y)
+
+
 def test_stream_forms_agree():
     """The default, object and integer streams, and a Parameter (a plain tensor
     to the native checks), give one result."""
